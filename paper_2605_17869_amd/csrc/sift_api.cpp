@@ -508,6 +508,7 @@ HdrPtrs header_ptrs(char* ws, int n) {
   hp.cand_prefix = reinterpret_cast<int*>(ws + hd.cand_prefix);
   hp.kp_prefix = reinterpret_cast<int*>(ws + hd.kp_prefix);
   hp.queue = reinterpret_cast<int*>(ws + hd.queue);
+  hp.ws = ws;
   return hp;
 }
 
@@ -687,7 +688,7 @@ sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, co
   if ((st = check_hip(launch_ori_scan(ws, hp, n, p, stream), "orientation scan")) != SIFT_OK) return st;
   if ((st = check_hip(launch_img_prefix(ws, hp, n, p, 1, stream), "prefix")) != SIFT_OK) return st;
   prof_end(prec, stream);
-  const int desc_grid = (int)std::min<int64_t>(4096, std::max<int64_t>(1, cand_total));
+  const int desc_grid = (int)std::min<int64_t>(1024, std::max<int64_t>(1, cand_total));
   prec = prof_begin(kStDescribe, 0.0, stream);
   if ((st = check_hip(launch_describe(ws, hp, n, p, desc_grid, stream), "describe")) != SIFT_OK) return st;
   prof_end(prec, stream);

@@ -137,14 +137,15 @@ __device__ __forceinline__ float atan2_poly(float y, float x) {
   constexpr float c[8] = {0.999999344f, -0.333298594f, 0.199465662f, -0.139086306f,
                           0.0964219868f, -0.0559123345f, 0.0218629558f, -0.00405456498f};
   const float ax = fabsf(x), ay = fabsf(y);
-  const float mx = fmaxf(ax, ay), mn = fminf(ax, ay);
+  const bool steep = ay > ax;
+  const float mx = steep ? ay : ax, mn = steep ? ax : ay;
   const float a = mx > 0.0f ? mn * __builtin_amdgcn_rcpf(mx) : 0.0f;
   const float s = a * a;
   float r = c[7];
 #pragma unroll
   for (int j = 6; j >= 0; --j) r = __fmaf_rn(r, s, c[j]);
   r = r * a;
-  if (ay > ax) r = 1.57079632679489662f - r;
+  if (steep) r = 1.57079632679489662f - r;
   if (x < 0.0f) r = 3.14159265358979324f - r;
   return y < 0.0f ? -r : r;
 }

@@ -30,7 +30,7 @@ constexpr int kXcds = 8;           // work-groups are dealt round-robin to the X
 constexpr int kMaxParts = 8;       // sub-batches (each with its own header) of one batched call
 constexpr int kBand = 8;           // rows per detection band
 constexpr int kDetectWaves = 4;    // waves of a detection work-group
-constexpr int kQueues = 1;         // work counters: descriptor
+constexpr int kQueues = 8;         // most work counters of the descriptor (one per XCD)
 constexpr int kSeg = 62;           // output columns per 64-lane detection segment
 constexpr int kOriBins = 36;
 constexpr int kMaxPeaks = kOriBins / 2;   // strict circular maxima of 36 bins
@@ -187,8 +187,10 @@ SIFT_HD void band_owner(int h, int w, const LayoutCfg& c, int lb, int* k_out, in
   *band_out = lb - bb;
 }
 
-// Counter slots inside an image region.
-enum Counter { kCntCand = 0, kCntKp = 1 };
+// Counter slots inside an image region; kCntQueue: work counter i of the launch
+// sequence, i = 1 .. kQueues - 1, in image i's region (far from each other and
+// from counter 0, which the header holds).
+enum Counter { kCntCand = 0, kCntKp = 1, kCntQueue = 2 };
 
 // One image of a batch as the kernels see it (written by the setup kernel).
 struct ImgEntry {
@@ -214,7 +216,7 @@ struct Header {
   int64_t band_prefix;     // int32 [n + 1]
   int64_t cand_prefix;     // int32 [n + 1]: refined candidates per image
   int64_t kp_prefix;       // int32 [n + 1]: described keypoints per image
-  int64_t queue;           // int32 [kQueues]: next work item of the per-keypoint kernels
+  int64_t queue;           // int32 [kQueues]: work counter 0 of the descriptor, the rest unused
   int64_t bytes;
 };
 
@@ -230,6 +232,7 @@ struct HdrPtrs {
   int* cand_prefix;        // int32 [n + 1]
   int* kp_prefix;          // int32 [n + 1]
   int* queue;              // int32 [kQueues]
+  char* ws;                // the workspace
 };
 
 SIFT_HD void make_header(int n, Header* hd) {

@@ -31,6 +31,11 @@ __global__ void k_setup(HdrPtrs hp, SetupChunk c) {
 // running total of table t between chunks.
 static_assert(kNumTileH * kMaxOct + 1 <= 64, "one lane per table");
 
+// Work counter i of the launch sequence (i < min(n, kQueues)).
+__device__ __forceinline__ int* work_counter(const HdrPtrs& hp, int i) {
+  return i == 0 ? hp.queue : &counters_of(hp.ws, hp.table[i])[kCntQueue];
+}
+
 __global__ void k_finalize(HdrPtrs hp, int n, DevParams p) {
   const ImgEntry* tab = hp.table;
   const LayoutCfg lc = layout_cfg(p);
@@ -65,7 +70,8 @@ __global__ void k_finalize(HdrPtrs hp, int n, DevParams p) {
       if (lane == t) run += chunk;
     }
   }
-  if (lane < kQueues) hp.queue[lane] = 0;   // the work counters of this launch sequence
+  // the work counters of this launch sequence
+  if (lane < min(n, kQueues)) *work_counter(hp, lane) = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -441,19 +447,73 @@ __global__ __launch_bounds__(256) void k_refine(char* ws, HdrPtrs hp, int n, Dev
 // keypoint (descriptor) prefix tables in LDS.
 constexpr int kOriLdsPrefix = 1024;
 constexpr int kDescLdsPrefix = 319;
+// Descriptor windows of at most this many 8 x 8 tiles form one stream, then two
+// (sides up to 69 and 101 pixels).  Each further stream costs a keypoint a
+// histogram cleared and summed and half an empty batch: at 49 and 81 tiles the
+// 64-image 1024x768 batch took 0.52 ms, at these 0.48 ms, with a single stream for
+// every window 0.49 ms; the largest windows then hold a launch of few keypoints
+// (one 640x480 image: 31, 35 and 35 us).
+constexpr int kDescOneStream = 81;
+constexpr int kDescTwoStreams = 169;
+// Keypoints per work-group up to which a keypoint's streams are shared by the
+// waves of a work-group.  8 images of 800x600 with five sizes (about 4,100
+// keypoints on 4096 waves): 0.46 ms with a wave per keypoint, 0.30 ms shared;
+// four times as many keypoints fill the waves either way.
+constexpr int kDescShareLimit = 4;
 
-// The next work item of a wave from a counter in the workspace header: one
-// integer atomic per item, taken by whichever wave asks first.  Each item's
-// results go to slots fixed by its index, so they do not depend on which
-// wave computed them; waves whose items cost less take more of them.  Used
-// where items are long and uneven (descriptors: the window grows with the
-// keypoint's scale); for short items (orientation, with many rejected
-// candidates) the atomics on one address cost more than the balance gains.
-__device__ __forceinline__ int next_item(int* counter) {
-  int v = 0;
-  if ((threadIdx.x & 63) == 0) v = atomicAdd(counter, 1);
-  return __shfl(v, 0, 64);
-}
+// Work items of a wave, out of `total` for the launch.  The items are split
+// evenly over up to kQueues counters; a work-group starts at the counter of its
+// XCD (work-groups are dealt to the XCDs in turn) and goes on to the others when
+// that one has run out.  A run of items is 1 / 4 of what would be the wave's
+// share of the items left, so the waves finish together although some items
+// cost several times others, and a wave asks for its next run as it starts the
+// last item of the one in hand.  Atomics on one address that all XCDs use
+// complete every 13 ns: a single counter and one item at a time held a launch
+// of 60,000 items at 0.8 ms.  Each item's results go to slots fixed by its
+// index, so they do not depend on which wave computed them.
+struct WorkRuns {
+  HdrPtrs hp;
+  int total, nq, waves;    // items; counters; waves per counter
+  int each, extra;         // items per counter; the first `extra` have one more
+  int q;                   // the counter in use
+  int turns = 0;           // counters found empty so far
+  int next = 0, end = 0;   // the run in hand
+  int run = 0, ticket = 0; // the run asked for (0: none) and the counter's answer
+  int left;                // items left at the counter at the last look
+  __device__ __forceinline__ WorkRuns(const HdrPtrs& h, int n, int items)
+      : hp(h), total(items), nq(min(n, kQueues)) {
+    waves = max((int)(gridDim.x * (blockDim.x / 64)) / nq, 1);
+    q = blockIdx.x % nq;
+    each = total / nq;
+    extra = total - each * nq;
+    left = each;
+  }
+  __device__ __forceinline__ void ask() {
+    run = min(max(left / (4 * waves), 1), 16);
+    if ((threadIdx.x & 63) == 0) ticket = atomicAdd(work_counter(hp, q), run);
+  }
+  // the next item, or total when there is none
+  __device__ __forceinline__ int pop() {
+    while (next == end && turns < nq) {
+      if (run == 0) ask();
+      const int v = __builtin_amdgcn_readfirstlane(ticket);
+      const int lo = q * each + min(q, extra);
+      const int n = each + (q < extra ? 1 : 0);
+      left = max(n - v - run, 0);
+      next = lo + min(v, n);
+      end = lo + min(v + run, n);
+      run = 0;
+      if (next == end) {
+        ++turns;
+        q = q + 1 == nq ? 0 : q + 1;
+      }
+    }
+    if (next == end) return total;
+    const int item = next++;
+    if (next == end && turns < nq) ask();
+    return item;
+  }
+};
 
 template <bool H16MODE>
 __global__ __launch_bounds__(256) void k_orient(char* ws, HdrPtrs hp, int n, DevParams p) {
@@ -649,75 +709,134 @@ __global__ __launch_bounds__(256) void k_ori_scan(char* ws, HdrPtrs hp, int n, D
 }
 
 // ---------------------------------------------------------------------------
-// Descriptor: one wave per output keypoint.  The bounding square of the
-// rotated 4x4 grid of the largest pooled domain size is scanned 64 samples at
-// a time; the samples whose rotated cell coordinates fall in (-1, 4) (about
-// 60% of the square) are packed, with their pixel gradients, into full
-// 64-lane batches by a lane permutation in registers, so the trilinear
-// binning runs with every lane busy; each packed pixel is binned for every
-// domain size whose window holds it.  Each lane accumulates into its own LDS column of the
-// 128-bin histogram.  Scan, packing and column order are fixed, so the sums
-// are too.  The lane columns are summed in a fixed order, averaged over domain
-// sizes, then L2-normalised, clamped, L2-normalised and optionally turned into
-// RootSIFT (L1 normalise, square root).
+// Descriptor.  A keypoint's window, the square that holds the rotated 4x4 grid
+// of the largest pooled domain size, is cut into tiles of 8 x 8 pixels around
+// the centre pixel, numbered ring by ring outwards.  64 tiles at a time, one
+// lane each, are tested against the rotated square, and the tiles that touch
+// it are scanned one per step, a pixel per lane: no division, one address per
+// lane and four loads from it.  The pixels inside the square (about 60 %) are
+// packed, with their rotated offsets and gradients, into full 64-lane batches
+// by a lane permutation in registers, so the trilinear binning runs with every
+// lane busy; each packed pixel is binned for every domain size whose window
+// holds it.  Taking the tiles ring by ring puts pixels of about the same
+// distance from the centre into one batch, which then leave the loop over the
+// sizes together (0.70 of the lanes busy over ten sizes; row by row 0.59).
+//
+// Streams.  The tiles of a window are dealt to 1, 2 or 4 streams by the window's
+// size alone; each stream packs its own pixels into an empty histogram, and the
+// streams' sums are added in order.  With many keypoints one wave takes a
+// keypoint's streams one after the other; with few (they would leave most of the
+// chip idle, and the largest window's wave would run alone for most of the
+// launch) each of the four waves of a work-group takes one stream.  The sums
+// are the same either way, so an image's descriptors do not depend on the
+// batch it is in.
+//
+// Bound: vector issue (0.85 of it for one size, 64 images of 1024x768) and LDS.
+// One instruction of the LDS takes the time of 64 lanes however few are active, so
+// the binning keeps all lanes active (see accumulate); with lanes that share a
+// column taking turns, four times as many LDS instructions, row-by-row scan order and
+// one work counter the launch took 0.84 ms, now 0.48 ms; 64 mixed images with ten
+// sizes 2.50 ms, now 1.07 ms; one 97x131 tile 81 us, now 28 us.  Float
+// atomics of the LDS were five times slower than reading, adding and writing
+// (they take lanes one by one).
+//
+// Scan, packing and column order are fixed, so the sums are too.  The columns
+// are summed in a fixed order, averaged over domain sizes, then L2-normalised,
+// clamped, L2-normalised and optionally turned into RootSIFT (L1 normalise,
+// square root).
+
+// Tile t of the window in units of tiles from the centre tile: t = 0 is the
+// centre, tiles (2r - 1)^2 .. (2r + 1)^2 - 1 run around ring r.
+__device__ __forceinline__ void ring_tile(int t, int& ti, int& tj) {
+  // r = floor((sqrt(t) + 1) / 2); the root of a square below 2^24 is exact
+  const int r = (int)((sqrtf((float)t) + 1.0f) * 0.5f);
+  const int k = t - (2 * r - 1) * (2 * r - 1);
+  const int q = (k >= 2 * r) + (k >= 4 * r) + (k >= 6 * r);
+  const int p = k - 2 * r * q - r;   // -r .. r - 1 along the side
+  ti = q == 0 ? p : (q == 1 ? r : (q == 2 ? -p : -r));
+  tj = q == 0 ? -r : (q == 1 ? p : (q == 2 ? r : -p));
+  if (t == 0) ti = tj = 0;
+}
+
+// max(0, 1 - |d|)
+__device__ __forceinline__ float hat(float d) {
+  return __builtin_amdgcn_fmed3f(1.0f - fabsf(d), 0.0f, 1.0f);
+}
+
+constexpr int kDescWaves = 4;
+
+// Histogram of a wave: 16 columns per bin.  Word of column w of orientation slot
+// o of cell (r, c): kHistRow2 (r / 2) + kHistCol2 (c / 2) + kHistOri o +
+// kHistRow (r % 2) + kHistCol (c % 2) + w.  The parities of the cell select the
+// bank, so lanes at cells of different parities never meet in one.  A cell has
+// nine slots: orientation 8 is 0 again, so a pixel's two slots are neighbours
+// (one instruction reads or writes both).
+constexpr int kHistCol = 16, kHistRow = 32, kHistOri = 64;
+constexpr int kHistCol2 = 9 * kHistOri, kHistRow2 = 2 * kHistCol2;
+constexpr int kHistWords = 2 * kHistRow2;
 
 // ND: the number of domain sizes the code is unrolled for (1, or the most).
-// The launch bound asks for 16 resident groups per CU (128 registers per
-// lane): the one-size build fits; the pooled-size build takes about 180
-// registers and 8 groups are resident per CU.
 // H16MODE: fp16 level storage is on; each keypoint's octave picks the path.
 template <int ND, bool H16MODE>
-__global__ __launch_bounds__(64, 16) void k_describe(char* ws, HdrPtrs hp, int n, DevParams p) {
-  // DC histogram columns: lanes l, l + DC, ... share column l % DC and add
-  // in turn.  Four lanes per column with one domain size; with several, two
-  // (their unrolled size loop needs the registers a third resident wave would)
-  constexpr int DC = ND == 1 ? 16 : 32, NG = 64 / DC;
-  __shared__ float hist[kDescDim * DC];
+__global__ __launch_bounds__(64 * kDescWaves)
+__attribute__((amdgpu_waves_per_eu(ND <= 10 ? 4 : 3)))
+void k_describe(char* ws, HdrPtrs hp, int n, DevParams p) {
+  __shared__ __align__(16) float s_hist[kDescWaves][kHistWords];
+  // a stream's sums, when the waves of the work-group share a keypoint
+  __shared__ float s_part[kDescWaves][kDescDim];
   // the keypoint prefix over the images, in LDS when it fits (kept small:
-  // the LDS of 16 resident waves per CU is nearly all histograms)
+  // the LDS is nearly all histograms)
   __shared__ int s_kpp[kDescLdsPrefix + 1];
   const int* kpp = hp.kp_prefix;
   const bool kpp_lds = n <= kDescLdsPrefix;
   if (kpp_lds) {
-    for (int i = threadIdx.x; i <= n; i += 64) s_kpp[i] = kpp[i];
-    wave_lds_sync();
+    for (int i = threadIdx.x; i <= n; i += 64 * kDescWaves) s_kpp[i] = kpp[i];
+    __syncthreads();
   }
   const int total = kpp[n];
   const ImgEntry* tab = hp.table;
   const LayoutCfg lc = layout_cfg(p);
-  const int lane = threadIdx.x;
-  int* const queue = hp.queue;
-  int g_next = next_item(queue);
-  for (int g = g_next; g < total; g = g_next) {
-    g_next = next_item(queue);   // the wave's next keypoint, fetched while this one runs
-    const int img = kpp_lds ? find_owner(s_kpp, n, g) : find_owner(kpp, n, g);
-    const int q = g - (kpp_lds ? s_kpp[img] : kpp[img]);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* const hist = s_hist[wave];
+  WorkRuns runs(hp, n, total);
+  const bool shared_kp = total <= kDescShareLimit * (int)gridDim.x;
+  int g = shared_kp ? (int)blockIdx.x : runs.pop();
+  while (g < total) {
+    // the next keypoint, fetched while this one runs
+    const int g_next = shared_kp ? g + (int)gridDim.x : runs.pop();
+    const int img = __builtin_amdgcn_readfirstlane(kpp_lds ? find_owner(s_kpp, n, g)
+                                                           : find_owner(kpp, n, g));
+    const int q = __builtin_amdgcn_readfirstlane(g - (kpp_lds ? s_kpp[img] : kpp[img]));
     const ImgEntry e = tab[img];
     const RegionTail rt = region_tail(e.h, e.w, lc);
-    const int* cnt = counters_of(ws, e);
     // the candidate and peak this keypoint slot describes (written by the
     // orientation scan)
     SIFT_CHECK_INDEX(q, p.max_kp);
-    const int src = reinterpret_cast<const int*>(ws + e.region + rt.kp_src)[q];
+    const int src = __builtin_amdgcn_readfirstlane(
+        reinterpret_cast<const int*>(ws + e.region + rt.kp_src)[q]);
     const int j = src >> 5;
     const int pk_idx = src & 31;
     const RefinedKp kp = reinterpret_cast<const RefinedKp*>(ws + e.region + rt.refined)[j];
-    const int4 cd = reinterpret_cast<const int4*>(ws + e.region + rt.cands)[j];
+    const int kr = __builtin_amdgcn_readfirstlane(kp.r), kc = __builtin_amdgcn_readfirstlane(kp.c);
+    const int k = __builtin_amdgcn_readfirstlane(kp.k);
+    const int layer = __builtin_amdgcn_readfirstlane(kp.layer);
     const float angle =
         reinterpret_cast<const float*>(ws + e.region + rt.angles)[(int64_t)j * kMaxPeaks + pk_idx];
-    const int k = kp.k;
     const OctView ov = octave_view(e.h, e.w, lc, k);
-    const int hk = ov.h, wk = ov.w, pk = ov.pitch;
-    const float* L = level_ptr(ws, e, ov, kp.layer);
+    const int hk = ov.h, wk = ov.w;
+    const int es = H16MODE ? ov.es : 4;
     SIFT_SPAN(rspan, region_span(ws, e, lc));
-    const gchar* gL = uniform_ptr(reinterpret_cast<const gchar*>(as_global(L)));
-    const uint32_t pkb = (uint32_t)pk * 4u;
+    // the four neighbours of a pixel: one byte offset from four uniform bases
+    const gchar* gL = uniform_ptr(reinterpret_cast<const gchar*>(as_global(level_ptr(ws, e, ov, layer))));
+    const uint32_t pkb = (uint32_t)ov.pitch * (uint32_t)es;
+    const gchar* gr = uniform_ptr(gL + es);
+    const gchar* gl = uniform_ptr(gL - es);
+    const gchar* gd = uniform_ptr(gL + pkb);
+    const gchar* gu = uniform_ptr(gL - pkb);
     const float th = angle * (kTwoPi / 360.0f);
-    const float st = sinf(th), ct = cosf(th);
-
-#pragma unroll
-    for (int bn = lane; bn < kDescDim * DC; bn += 64) hist[bn] = 0.0f;
-    wave_lds_sync();
+    float st, ct;
+    sincosf(th, &st, &ct);
 
     // Domain sizes: a pixel inside the window of one size is inside the
     // window of every larger one (the cell test is monotone in 1 / cell, in
@@ -727,14 +846,18 @@ __global__ __launch_bounds__(64, 16) void k_describe(char* ws, HdrPtrs hp, int n
     // the sizes come sorted, largest first
     const float smax = p.dsp[0];
     const float wc_max = p.desc_magnif * kp.sigma_oct * smax;
-    const float inv_max = 1.0f / wc_max;
     // A sample contributes only if its rotated cell coordinates fall in
     // (-1, 4), i.e. |u|, |v| < 2.5 wc (|cos| + |sin|) around the sub-pixel
     // centre; one extra ring covers the sub-pixel offset and fp32 rounding.
-    const int R = (int)ceilf(2.5f * wc_max * (fabsf(ct) + fabsf(st))) + 1;
-    const int side = 2 * R + 1;
-    const int nsamp = side * side;
-    const float inv_side = 1.0f / (float)side;
+    const float spread = fabsf(ct) + fabsf(st);
+    const int R = __builtin_amdgcn_readfirstlane((int)ceilf(2.5f * wc_max * spread) + 1);
+    // tile i covers pixels 8 i - 4 .. 8 i + 3, so tiles -m .. m cover -R .. R
+    const int m = (R + 4) >> 3;
+    const int ntiles = (2 * m + 1) * (2 * m + 1);
+    const int nstreams = ntiles <= kDescOneStream ? 1 : (ntiles <= kDescTwoStreams ? 2 : 4);
+    // a tile whose centre lies this far out (in the rotated frame) holds no
+    // pixel of the window (3.5 pixels to its outermost ones; rounding margin)
+    const float reach = 2.5f * wc_max * 1.0001f + 3.5f * spread + 0.01f;
     // 1 / cell size of every domain size, and the factor that turns a
     // squared pixel distance into the base-2 exponent of the grid's Gaussian
     // weight exp(-(xr^2 + yr^2) / 8) for that size (unused entries 0)
@@ -745,230 +868,255 @@ __global__ __launch_bounds__(64, 16) void k_describe(char* ws, HdrPtrs hp, int n
       gk_ws[ds] = inv_ws[ds] * inv_ws[ds] * (-0.125f * 1.44269504088896341f);
     }
 
-    // rotated offset (dx, dy) from the sub-pixel centre, in pixels
-    auto rotate = [&](int dx, int dy, float& xr0, float& yr0) {
-      const float fu = (float)dx - kp.dx;
-      const float fv = (float)dy - kp.dy;
-      xr0 = ct * fu + st * fv;
-      yr0 = ct * fv - st * fu;
-    };
-    // rotated cell coordinates (xr, yr) relative to the grid centre: inside
-    // (-1, 4) after the shift by 1.5, i.e. both below 2.5 in magnitude
-    auto in_window = [](float xr, float yr) { return fmaxf(fabsf(xr), fabsf(yr)) < 2.5f; };
-    // trilinear binning of one contributing pixel into this lane's column,
-    // once per domain size whose window holds it; every lane of the wave
-    // takes part (lanes with valid == false add nothing)
-    auto accumulate = [&](int pxy, float gx, float gy, bool valid) {
-      const int dx = (int)(short)(pxy & 0xffff), dy = pxy >> 16;
-      float xr0, yr0;
-      rotate(dx, dy, xr0, yr0);
+    // Half the side of every window, in pixels: 2.5 cells.
+    float lim_ws[ND];
+#pragma unroll
+    for (int ds = 0; ds < ND; ++ds)
+      lim_ws[ds] = ds < p.n_dsp ? 2.5f * (p.desc_magnif * kp.sigma_oct * p.dsp[ds]) : 0.0f;
+    // Trilinear binning of one contributing pixel into this lane's column, once
+    // per domain size whose window holds it; every lane of the wave takes part
+    // (lanes with valid == false add nothing).  A pixel reaches one even and one
+    // odd grid row, one even and one odd grid column: the nearest of each,
+    // with weight max(0, 1 - distance) (+0 for one it does not reach; adding
+    // +0 to a non-negative sum leaves it unchanged).  In step (a, b) every lane
+    // adds to one cell; the four lanes that share a column (lanes l, l + 16,
+    // l + 32, l + 48) are then at cells of the four different parities, so no two
+    // lanes of a step touch the same word.
+    const int par_r = lane >> 5 & 1, par_c = lane >> 4 & 1;   // parities of step (0, 0)
+    const float kr0 = par_r ? -0.5f : 0.5f, kc0 = par_c ? -0.5f : 0.5f;
+    char* base[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        base[a][b] = reinterpret_cast<char*>(hist) +
+                     4 * (kHistRow * (par_r ^ a) + kHistCol * (par_c ^ b) + (lane & 15));
+    auto accumulate = [&](float xr0, float yr0, float gx, float gy, bool valid) {
       const float r2 = xr0 * xr0 + yr0 * yr0;
+      const float far = fmaxf(fabsf(xr0), fabsf(yr0));
       const float mag = __builtin_amdgcn_sqrtf(gx * gx + gy * gy);
-      float ta = atan2_poly(gy, gx);
-      if (ta < 0.0f) ta += kTwoPi;
-      float ob = ta - th;
-      if (ob < 0.0f) ob += kTwoPi;
-      if (ob >= kTwoPi) ob -= kTwoPi;
-      ob = ob * (8.0f / kTwoPi);
+      // orientation bin: the angle from the keypoint's, in eighths of a turn
+      const float ob = __builtin_amdgcn_fractf((atan2_poly(gy, gx) - th) * (1.0f / kTwoPi)) * 8.0f;
       const float o0 = floorf(ob);
-      const float fo = ob - o0;
-      int io = (int)o0;
-      if (io >= 8) io -= 8;
-      const int io1 = (io + 1) & 7;
-      const int col = lane & (DC - 1);
+      const float fo = ob - o0, fo1 = 1.0f - fo;
+      const int at_lo = (int)o0 * (4 * kHistOri), at_hi = at_lo + 4 * kHistCol2;
 #pragma unroll
       for (int ds = 0; ds < ND; ++ds) {
         if (ds >= p.n_dsp) break;
-        const float xr = xr0 * inv_ws[ds], yr = yr0 * inv_ws[ds];
         // with one size the scan's window test was this very test
-        const bool add = valid && (ND == 1 || in_window(xr, yr));
+        const bool add = valid && (ND == 1 || far < lim_ws[ds]);
         // sizes run largest first, and a pixel outside one size's window is
         // outside every smaller one's: once no lane adds, none will again
         if (ND > 1 && __ballot(add) == 0ull) break;
         const float wgt = mag * __builtin_amdgcn_exp2f(r2 * gk_ws[ds]);
-        // The sample updates the 2 x 2 grid cells from (floor(rb), floor(cb))
-        // clamped to 0..2, so the eight targets are always on the grid and
-        // distinct.  A cell at distance d (in cells) from the sample along an
-        // axis gets weight max(0, 1 - |d|): the bilinear weight for the two
-        // cells the sample reaches, +0 for a block row or column it does not
-        // reach (adding +0 to a non-negative sum leaves it unchanged).
-        const float rb = yr + 1.5f, cb = xr + 1.5f;
-        const float r0 = __builtin_amdgcn_fmed3f(floorf(rb), 0.0f, 2.0f);
-        const float c0 = __builtin_amdgcn_fmed3f(floorf(cb), 0.0f, 2.0f);
-        const float dr = rb - r0, dc = cb - c0;
-        const float wr[2] = {fmaxf(1.0f - fabsf(dr), 0.0f), fmaxf(1.0f - fabsf(dr - 1.0f), 0.0f)};
-        const float wc[2] = {fmaxf(1.0f - fabsf(dc), 0.0f), fmaxf(1.0f - fabsf(dc - 1.0f), 0.0f)};
-        const float wo[2] = {wgt * (1.0f - fo), wgt * fo};
-        // a lane that adds nothing keeps its (unused) addresses on the grid
-        const int cell = add ? (int)(r0 * 4.0f + c0) : 0;
-        float* h0 = &hist[(cell * 8 + io) * DC + col];
-        float* h1 = &hist[(cell * 8 + io1) * DC + col];
-        // the eight targets: cells cell .. cell + 5 (rows +0/+1, columns +0/+1)
-        SIFT_CHECK_INDEX((cell * 8 + io) * DC + col, kDescDim * DC);
-        SIFT_CHECK_INDEX(((cell + 5) * 8 + io1) * DC + col, kDescDim * DC);
-        float wv[8];
+        // signed distances, in cells, from row 1 (even rows: 0 and 2 are one
+        // away from it) or 2 (odd rows), and from column 1 or 2
+        const float tr[2] = {__fmaf_rn(yr0, inv_ws[ds], kr0), __fmaf_rn(yr0, inv_ws[ds], -kr0)};
+        const float tc[2] = {__fmaf_rn(xr0, inv_ws[ds], kc0), __fmaf_rn(xr0, inv_ws[ds], -kc0)};
+        const float wr[2] = {hat(fabsf(tr[0]) - 1.0f), hat(fabsf(tr[1]) - 1.0f)};
+        const float wc[2] = {hat(fabsf(tc[0]) - 1.0f), hat(fabsf(tc[1]) - 1.0f)};
+        const float wo0 = wgt * fo1, wo1 = wgt * fo;
+        if (add) {
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const float ra0 = wr[a] * wo[0], ra1 = wr[a] * wo[1];
+          for (int a = 0; a < 2; ++a) {
+            const float ra0 = wr[a] * wo0, ra1 = wr[a] * wo1;
+            const int row = tr[a] < 0.0f ? 0 : 4 * kHistRow2;
 #pragma unroll
-          for (int bb = 0; bb < 2; ++bb) {
-            wv[4 * a + 2 * bb] = ra0 * wc[bb];
-            wv[4 * a + 2 * bb + 1] = ra1 * wc[bb];
-          }
-        }
-        // the lane groups sharing a column update it in turn, each with its
-        // own instructions: read the eight targets, then write them
-#pragma unroll
-        for (int grp = 0; grp < NG; ++grp) {
-          if (add && lane / DC == grp) {
-            float hv[8];
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-#pragma unroll
-              for (int bb = 0; bb < 2; ++bb) {
-                const int off = (a * 4 + bb) * 8 * DC;   // cell step: 8 bins of DC columns
-                hv[4 * a + 2 * bb] = h0[off];
-                hv[4 * a + 2 * bb + 1] = h1[off];
-              }
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-#pragma unroll
-              for (int bb = 0; bb < 2; ++bb) {
-                const int off = (a * 4 + bb) * 8 * DC;
-                h0[off] = hv[4 * a + 2 * bb] + wv[4 * a + 2 * bb];
-                h1[off] = hv[4 * a + 2 * bb + 1] + wv[4 * a + 2 * bb + 1];
-              }
+            for (int b = 0; b < 2; ++b) {
+              float* const h = reinterpret_cast<float*>(base[a][b] + (row + (tc[b] < 0.0f ? at_lo : at_hi)));
+              SIFT_CHECK_INDEX(h - hist, kHistWords - kHistOri);
+              const float s0 = h[0], s1 = h[kHistOri];
+              h[0] = s0 + ra0 * wc[b];
+              h[kHistOri] = s1 + ra1 * wc[b];
+              // keeps the steps' updates in separate instructions, in order
+              wave_lds_sync();
             }
           }
-          // keeps the groups' updates in separate instructions, in order
-          __builtin_amdgcn_wave_barrier();
         }
       }
     };
 
-    // Pending contributing pixels sit in lanes [0, fill): packed offset
-    // (dy << 16 | dx & 0xffff) and gradient.
-    int fill = 0;
-    int p_xy = 0;
-    float p_gx = 0.0f, p_gy = 0.0f;
-    constexpr int U = 4;   // scan batches whose loads are issued together
-    for (int q0 = 0; q0 < nsamp; q0 += 64 * U) {
-      float ga[U], gb[U], gc[U], gd[U];
-      int sxy[U];
-      bool ok[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int qq = q0 + 64 * u + lane;
-        // qq / side: an fp32 estimate within one of the quotient, then one
-        // correction step on the remainder makes it exact
-        int qy = (int)(((float)qq + 0.5f) * inv_side);
-        int qx = qq - qy * side;
-        if (qx < 0) {
-          --qy;
-          qx += side;
-        } else if (qx >= side) {
-          ++qy;
-          qx -= side;
-        }
-        const int dy = qy - R, dx = qx - R;
-        const int rr = kp.r + dy, cc = kp.c + dx;
-        float xr0, yr0;
-        rotate(dx, dy, xr0, yr0);
-        ok[u] = qq < nsamp && rr >= 1 && rr <= hk - 2 && cc >= 1 && cc <= wk - 2 &&
-                in_window(xr0 * inv_max, yr0 * inv_max);
-        sxy[u] = (dy << 16) | (dx & 0xffff);
-        // samples that do not contribute read the (interior) centre instead
-        const uint32_t idx = (uint32_t)((ok[u] ? rr : kp.r) * pk + (ok[u] ? cc : kp.c));
-        SIFT_CHECK_IN(rspan, gL + (uint64_t)idx * ov.es - (uint64_t)pk * ov.es, ov.es);
-        SIFT_CHECK_IN(rspan, gL + (uint64_t)idx * ov.es + (uint64_t)pk * ov.es, ov.es);
-        if (H16MODE && ov.es == 2) {
-          const uint32_t at = idx * 2u, pkh = (uint32_t)pk * 2u;
-          ga[u] = load_lv<true>(gL, at + 2u);
-          gb[u] = load_lv<true>(gL, at - 2u);
-          gc[u] = load_lv<true>(gL, at + pkh);
-          gd[u] = load_lv<true>(gL, at - pkh);
-        } else {
-          const uint32_t at = idx * 4u;
-          ga[u] = load_at(gL, at + 4u);
-          gb[u] = load_at(gL, at - 4u);
-          gc[u] = load_at(gL, at + pkb);
-          gd[u] = load_at(gL, at - pkb);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint64_t m = __ballot(ok[u]);
-        const int cnt = __popcll(m);
-        const int rank = __popcll(m & lanemask_lt());
-        // contributing lanes go to [fill, fill + cnt), the others after them
-        const int dest = (ok[u] ? fill + rank : fill + cnt + (lane - rank)) & 63;
-        const int r_xy = lane_send(dest, sxy[u]);
-        const float r_gx = lane_send(dest, ga[u] - gb[u]);
-        const float r_gy = lane_send(dest, gc[u] - gd[u]);
-        const int nf = fill + cnt;
-        if (nf >= 64) {
-          // lanes [fill, 64) complete the batch; lanes [0, nf - 64) overflow
-          const bool fresh = lane >= fill;
-          accumulate(fresh ? r_xy : p_xy, fresh ? r_gx : p_gx, fresh ? r_gy : p_gy, true);
-          p_xy = r_xy;
-          p_gx = r_gx;
-          p_gy = r_gy;
-          fill = nf - 64;
-        } else {
-          const bool take = lane >= fill && lane < nf;
-          p_xy = take ? r_xy : p_xy;
-          p_gx = take ? r_gx : p_gx;
-          p_gy = take ? r_gy : p_gy;
-          fill = nf;
-        }
-      }
-    }
-    accumulate(p_xy, p_gx, p_gy, lane < fill);
-    wave_lds_sync();
+    const int lx = (lane & 7) - 4, ly = (lane >> 3) - 4;   // the lane's pixel of tile (0, 0)
+    // rows and columns with both neighbours are 1 .. hk - 2 and 1 .. wk - 2
+    const int row1 = kr + ly - 1, col1 = kc + lx - 1;   // row - 1 and column - 1 in tile (0, 0)
+    const uint32_t centre = (uint32_t)kr * pkb + (uint32_t)(kc * es);
+    uint32_t at0 = centre + (uint32_t)(ly * (int)pkb + lx * es);
+    // kept as one value: a tile's address is then one addition away
+    __asm__("" : "+v"(at0));
     float h0 = 0.0f, h1 = 0.0f;
-    for (int t = 0; t < DC; ++t) {
-      const int col = (lane + t) & (DC - 1);
-      h0 += hist[lane * DC + col];
-      h1 += hist[(lane + 64) * DC + col];
+    for (int stream = shared_kp ? wave : 0; stream < nstreams;
+         stream += shared_kp ? kDescWaves : 1) {
+#pragma unroll
+      for (int i = 0; i < kHistWords / 256; ++i)
+        *reinterpret_cast<f32x4*>(&hist[4 * (64 * i + lane)]) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      wave_lds_sync();
+      // the stream's tiles within 64 consecutive ones
+      const uint64_t mine = nstreams == 1 ? ~0ull
+                            : (nstreams == 2 ? 0x5555555555555555ull : 0x1111111111111111ull)
+                                  << stream;
+      // Pending contributing pixels sit in lanes [0, fill): rotated offset
+      // and gradient.
+      int fill = 0;
+      float p_x = 0.0f, p_y = 0.0f, p_gx = 0.0f, p_gy = 0.0f;
+      for (int t0 = 0; t0 < ntiles; t0 += 64) {
+        int ti, tj;
+        ring_tile(t0 + lane, ti, tj);
+        const float fu = 8.0f * (float)ti - 0.5f - kp.dx, fv = 8.0f * (float)tj - 0.5f - kp.dy;
+        const bool touch = t0 + lane < ntiles &&
+                           fmaxf(fabsf(ct * fu + st * fv), fabsf(ct * fv - st * fu)) < reach;
+        const int tij = (tj << 16) | (ti & 0xffff);
+        uint64_t todo = __ballot(touch) & mine;
+        while (todo) {
+          constexpr int U = 4;   // tiles whose loads are issued together
+          float ga[U], gb[U], gc[U], ge[U], xr[U], yr[U];
+          uint64_t inside[U];   // the tile's lanes that contribute
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const bool some = todo != 0ull;
+            const int bit = some ? __builtin_ctzll(todo) : 0;
+            todo &= todo - 1ull;
+            const int xy = __builtin_amdgcn_readlane(tij, bit);
+            const int tx = 8 * (int)(short)(xy & 0xffff), ty = 8 * (xy >> 16);
+            // rotated offset from the sub-pixel centre, in pixels
+            const float u0 = (float)(lx + tx) - kp.dx;
+            const float v0 = (float)(ly + ty) - kp.dy;
+            xr[u] = ct * u0 + st * v0;
+            yr[u] = ct * v0 - st * u0;
+            const bool ok = ((uint32_t)(row1 + ty) < (uint32_t)(hk - 2)) &
+                            ((uint32_t)(col1 + tx) < (uint32_t)(wk - 2)) &
+                            (fmaxf(fabsf(xr[u]), fabsf(yr[u])) < lim_ws[0]);
+            inside[u] = some ? __ballot(ok) : 0ull;
+            // samples that do not contribute read the (interior) centre instead
+            const uint32_t at = ok ? at0 + (uint32_t)(ty * (int)pkb + tx * es) : centre;
+            SIFT_CHECK_IN(rspan, gu + at, es);
+            SIFT_CHECK_IN(rspan, gd + at, es);
+            if (H16MODE && es == 2) {
+              ga[u] = load_lv<true>(gr, at);
+              gb[u] = load_lv<true>(gl, at);
+              gc[u] = load_lv<true>(gd, at);
+              ge[u] = load_lv<true>(gu, at);
+            } else {
+              ga[u] = load_at(gr, at);
+              gb[u] = load_at(gl, at);
+              gc[u] = load_at(gd, at);
+              ge[u] = load_at(gu, at);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int cnt = __popcll(inside[u]);
+            // contributing lanes go to [fill, fill + cnt), the others after them
+            const int to = (int)__builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(inside[u] >> 32),
+                __builtin_amdgcn_mbcnt_lo((uint32_t)inside[u], (uint32_t)fill));
+            const int dest = __builtin_amdgcn_inverse_ballot_w64(inside[u])
+                                 ? to : lane + (2 * fill + cnt) - to;
+            const float r_x = lane_send(dest & 63, xr[u]);
+            const float r_y = lane_send(dest & 63, yr[u]);
+            const float r_gx = lane_send(dest & 63, ga[u] - gb[u]);
+            const float r_gy = lane_send(dest & 63, gc[u] - ge[u]);
+            const bool fresh = lane >= fill;
+            const float n_x = fresh ? r_x : p_x, n_y = fresh ? r_y : p_y;
+            const float n_gx = fresh ? r_gx : p_gx, n_gy = fresh ? r_gy : p_gy;
+            fill += cnt;
+            if (fill >= 64) {
+              // a full batch; lanes [0, fill - 64) of what was sent overflow it
+              accumulate(n_x, n_y, n_gx, n_gy, true);
+              p_x = r_x;
+              p_y = r_y;
+              p_gx = r_gx;
+              p_gy = r_gy;
+              fill -= 64;
+            } else {
+              p_x = n_x;
+              p_y = n_y;
+              p_gx = n_gx;
+              p_gy = n_gy;
+            }
+          }
+        }
+      }
+      accumulate(p_x, p_y, p_gx, p_gy, lane < fill);
+      wave_lds_sync();
+      // the stream's sums: bins lane and lane + 64 (two grid rows on), the
+      // columns of a bin taken from a start that differs between lanes
+      auto bin_sum = [&](const float* h) {
+        float v = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(&h[4 * ((lane + t) & 3)]);
+          v += (x.x + x.y) + (x.z + x.w);
+        }
+        return v;
+      };
+      const int cr = lane >> 5, cc = lane >> 3 & 3;   // the bin's cell: row 0 or 1 and column
+      const float* const hb = hist + kHistRow * cr + kHistCol2 * (cc >> 1) + kHistCol * (cc & 1) +
+                              kHistOri * (lane & 7);
+      float a0 = bin_sum(hb), a1 = bin_sum(hb + kHistRow2);
+      if ((lane & 7) == 0) {   // the slot past the last orientation is the first one
+        a0 += bin_sum(hb + 8 * kHistOri);
+        a1 += bin_sum(hb + kHistRow2 + 8 * kHistOri);
+      }
+      wave_lds_sync();
+      if (shared_kp) {
+        s_part[wave][lane] = a0;
+        s_part[wave][lane + 64] = a1;
+      } else {
+        h0 = stream == 0 ? a0 : h0 + a0;
+        h1 = stream == 0 ? a1 : h1 + a1;
+      }
     }
-    const float kf = (float)p.n_dsp;
-    h0 = h0 / kf;
-    h1 = h1 / kf;
-    float nrm = sqrtf(wave_sum(h0 * h0 + h1 * h1));
-    if (nrm > 0.0f) { h0 = h0 / nrm; h1 = h1 / nrm; } else { h0 = 0.0f; h1 = 0.0f; }
-    h0 = fminf(h0, p.desc_clamp);
-    h1 = fminf(h1, p.desc_clamp);
-    nrm = sqrtf(wave_sum(h0 * h0 + h1 * h1));
-    if (nrm > 0.0f) { h0 = h0 / nrm; h1 = h1 / nrm; } else { h0 = 0.0f; h1 = 0.0f; }
-    if (p.rootsift) {
-      const float l1 = wave_sum(fabsf(h0) + fabsf(h1));
-      if (l1 > 0.0f) { h0 = h0 / l1; h1 = h1 / l1; }
-      h0 = sqrtf(h0);
-      h1 = sqrtf(h1);
+    if (shared_kp) {
+      __syncthreads();
+      if (wave == 0) {
+        h0 = s_part[0][lane];
+        h1 = s_part[0][lane + 64];
+        for (int s = 1; s < nstreams; ++s) {
+          h0 += s_part[s][lane];
+          h1 += s_part[s][lane + 64];
+        }
+      }
+      __syncthreads();   // read before the next keypoint's sums are stored
     }
-    const int slot = q;
-    SIFT_CHECK_INDEX(slot, e.cap);
-    float* dout = e.desc + (int64_t)slot * kDescDim;
-    dout[lane] = h0;
-    dout[lane + 64] = h1;
-    if (lane == 0) {
-      sift_keypoint o;
-      o.x = kp.x;
-      o.y = kp.y;
-      o.sigma = kp.sigma;
-      o.angle = angle;
-      o.response = kp.response;
-      o.octave = p.o0 + k;
-      o.layer = kp.layer;
-      o.ix = kp.c;
-      o.iy = kp.r;
-      o.src_layer = cd.y;
-      o.src_iy = cd.z;
-      o.src_ix = cd.w;
-      e.kp[slot] = o;
+    if (!shared_kp || wave == 0) {
+      const float kf = (float)p.n_dsp;
+      h0 = h0 / kf;
+      h1 = h1 / kf;
+      float nrm = sqrtf(wave_sum(h0 * h0 + h1 * h1));
+      if (nrm > 0.0f) { h0 = h0 / nrm; h1 = h1 / nrm; } else { h0 = 0.0f; h1 = 0.0f; }
+      h0 = fminf(h0, p.desc_clamp);
+      h1 = fminf(h1, p.desc_clamp);
+      nrm = sqrtf(wave_sum(h0 * h0 + h1 * h1));
+      if (nrm > 0.0f) { h0 = h0 / nrm; h1 = h1 / nrm; } else { h0 = 0.0f; h1 = 0.0f; }
+      if (p.rootsift) {
+        const float l1 = wave_sum(fabsf(h0) + fabsf(h1));
+        if (l1 > 0.0f) { h0 = h0 / l1; h1 = h1 / l1; }
+        h0 = sqrtf(h0);
+        h1 = sqrtf(h1);
+      }
+      SIFT_CHECK_INDEX(q, e.cap);
+      float* dout = e.desc + (int64_t)q * kDescDim;
+      dout[lane] = h0;
+      dout[lane + 64] = h1;
+      if (lane == 0) {
+        const int4 cd = reinterpret_cast<const int4*>(ws + e.region + rt.cands)[j];
+        sift_keypoint o;
+        o.x = kp.x;
+        o.y = kp.y;
+        o.sigma = kp.sigma;
+        o.angle = angle;
+        o.response = kp.response;
+        o.octave = p.o0 + k;
+        o.layer = layer;
+        o.ix = kc;
+        o.iy = kr;
+        o.src_layer = cd.y;
+        o.src_iy = cd.z;
+        o.src_ix = cd.w;
+        e.kp[q] = o;
+      }
     }
-    wave_lds_sync();
+    g = g_next;
   }
 }
 
@@ -1036,8 +1184,8 @@ hipError_t launch_describe(char* ws, const HdrPtrs& hp, int n, const DevParams& 
   // the smallest unrolled size count that covers n_dsp (5: the paper's
   // pooling set, 10: the linearly spaced set of its benchmark)
 #define SIFT_DESCRIBE(NDD)                                                         \
-  return p.h16 ? launch(k_describe<NDD, true>, dim3(grid), dim3(64), stream, ws, hp, n, p) \
-               : launch(k_describe<NDD, false>, dim3(grid), dim3(64), stream, ws, hp, n, p)
+  return p.h16 ? launch(k_describe<NDD, true>, dim3(grid), dim3(64 * kDescWaves), stream, ws, hp, n, p) \
+               : launch(k_describe<NDD, false>, dim3(grid), dim3(64 * kDescWaves), stream, ws, hp, n, p)
   if (p.n_dsp == 1) SIFT_DESCRIBE(1);
   if (p.n_dsp <= 5) SIFT_DESCRIBE(5);
   if (p.n_dsp <= 10) SIFT_DESCRIBE(10);
