@@ -1,5 +1,5 @@
 // Host runtime of descriptor matching: argument checks, workspace layout and
-// the launch sequence (setup, similarity tiles, column reduction, emission).
+// the launch sequence (setup, nearest neighbours, merge of chunks, emission).
 // Like extraction, it never allocates device memory, copies or synchronises.
 #include <hip/hip_runtime.h>
 
@@ -29,9 +29,11 @@ int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
 int cdiv_i(int a, int b) { return (a + b - 1) / b; }
 
 struct MatchLayout {
-  int64_t table, row_prefix, col_prefix, header;
-  std::vector<int64_t> rowbest, colbest, colpart;
-  std::vector<int> rtiles, cblocks;
+  int64_t table, row_prefix, col_prefix;
+  std::vector<int64_t> best, part, half;
+  int chunks = 1;   // parts of a walk over the other set
+  int own_rows = kMatchTile;
+  bool half_copies = false, merge = false;
   int64_t bytes;
 };
 
@@ -56,7 +58,19 @@ sift_status check_pairs(int32_t n, const sift_match_pair* pairs) {
   return SIFT_OK;
 }
 
-MatchLayout layout_of(int32_t n, const sift_match_pair* pairs) {
+// Work-groups of the nearest-neighbour kernel that fill the chip: two on each
+// of 256 CUs (32 pairs of 2000 x 2000: 512 row tiles, 0.114 ms; in two parts each 0.123).
+constexpr int64_t kMatchTargetGroups = 512;
+// Similarity tiles from which the sets are first copied to fp16: below, a tile
+// is staged so few times that a launch of its own costs more than converting
+// it again (one pair of 2000 x 2000: 256 tiles; 8192 x 7900: 3968).
+constexpr int64_t kMatchHalfTiles = 1024;
+// Rows of a pair's sets up to which the emission merges the chunks itself.
+constexpr int64_t kMatchEmitMergeRows = 2048;
+
+// The plan of a call and its workspace.  `lean`: no chunks and no copies, the
+// least a call can run in.
+MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool lean) {
   MatchLayout L;
   int64_t off = 0;
   L.table = off;
@@ -65,17 +79,35 @@ MatchLayout layout_of(int32_t n, const sift_match_pair* pairs) {
   off = align256(off + (int64_t)(n + 1) * 4);
   L.col_prefix = off;
   off = align256(off + (int64_t)(n + 1) * 4);
-  L.header = off;
+  if (!lean) {
+    int64_t row_tiles = 0, tiles = 0;
+    int most_tiles = 0, most_rows = 0;
+    for (int i = 0; i < n; ++i) {
+      const int ta = cdiv_i(pairs[i].cap_a, kMatchTile), tb = cdiv_i(pairs[i].cap_b, kMatchTile);
+      row_tiles += ta + tb;
+      tiles += (int64_t)ta * tb;
+      most_tiles = std::max(most_tiles, std::max(ta, tb));
+      most_rows = std::max(most_rows, pairs[i].cap_a + pairs[i].cap_b);
+    }
+    L.half_copies = tiles >= kMatchHalfTiles;
+    if (L.half_copies) {
+      L.own_rows = kMatchOwnHalf;
+      row_tiles = 0;
+      for (int i = 0; i < n; ++i)
+        row_tiles += cdiv_i(pairs[i].cap_a, L.own_rows) + cdiv_i(pairs[i].cap_b, L.own_rows);
+    }
+    const int64_t want = row_tiles > 0 ? (kMatchTargetGroups + row_tiles - 1) / row_tiles : 1;
+    L.chunks = (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min(most_tiles, kMatchMaxChunks)));
+    L.merge = L.chunks > 1 && most_rows > kMatchEmitMergeRows;
+  }
   for (int i = 0; i < n; ++i) {
-    const int rt = cdiv_i(pairs[i].cap_a, kMatchTile);
-    L.rtiles.push_back(rt);
-    L.cblocks.push_back(cdiv_i(pairs[i].cap_b, kMatchColBlock));
-    L.rowbest.push_back(off);
-    off = align256(off + (int64_t)pairs[i].cap_a * (int64_t)sizeof(Top2));
-    L.colbest.push_back(off);
-    off = align256(off + (int64_t)pairs[i].cap_b * (int64_t)sizeof(Top2));
-    L.colpart.push_back(off);
-    off = align256(off + (int64_t)pairs[i].cap_b * rt * (int64_t)sizeof(Top2));
+    const int64_t rows = (int64_t)pairs[i].cap_a + pairs[i].cap_b;
+    L.best.push_back(off);
+    off = align256(off + rows * (int64_t)sizeof(Top2));
+    L.part.push_back(off);
+    if (L.chunks > 1) off = align256(off + rows * L.chunks * (int64_t)sizeof(Top2));
+    L.half.push_back(off);
+    if (L.half_copies) off = align256(off + rows * 128 * 2);
   }
   L.bytes = off;
   return L;
@@ -89,7 +121,7 @@ sift_status sift_match_workspace_size(int32_t n, const sift_match_pair* pairs, s
   if (!bytes) return fail(SIFT_ERR_INVALID_ARG, "null bytes");
   sift_status st = check_pairs(n, pairs);
   if (st != SIFT_OK) return st;
-  *bytes = (size_t)layout_of(n, pairs).bytes;
+  *bytes = (size_t)layout_of(n, pairs, false).bytes;
   return SIFT_OK;
 }
 
@@ -101,7 +133,8 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   if (!d_workspace) return fail(SIFT_ERR_INVALID_ARG, "null workspace");
   if (reinterpret_cast<uintptr_t>(d_workspace) % 256)
     return fail(SIFT_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-  const MatchLayout L = layout_of(n, pairs);
+  MatchLayout L = layout_of(n, pairs, false);
+  if ((int64_t)workspace_bytes < L.bytes) L = layout_of(n, pairs, true);
   if ((int64_t)workspace_bytes < L.bytes)
     return fail(SIFT_ERR_WORKSPACE_TOO_SMALL, "workspace " + std::to_string(workspace_bytes) +
                                                   " bytes, need " + std::to_string(L.bytes));
@@ -112,12 +145,19 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   h.table = reinterpret_cast<const MatchEntry*>(ws + L.table);
   h.row_prefix = reinterpret_cast<int*>(ws + L.row_prefix);
   h.col_prefix = reinterpret_cast<int*>(ws + L.col_prefix);
+  h.chunks = L.chunks;
+  h.half = L.half_copies ? 1 : 0;
+  h.merged = 0;
+  h.own_rows = L.own_rows;
 
   std::vector<int> rp(n + 1, 0), cp(n + 1, 0);
   for (int i = 0; i < n; ++i) {
-    rp[i + 1] = rp[i] + L.rtiles[i];
-    cp[i + 1] = cp[i] + L.cblocks[i];
+    rp[i + 1] = rp[i] + cdiv_i(pairs[i].cap_a, L.own_rows) + cdiv_i(pairs[i].cap_b, L.own_rows);
+    cp[i + 1] = cp[i] + cdiv_i(pairs[i].cap_a + pairs[i].cap_b, kMatchMergeBlock);
   }
+  h.same_tiles = rp[1];
+  for (int i = 1; i < n; ++i)
+    if (rp[i + 1] - rp[i] != rp[1]) h.same_tiles = 0;
   auto hip_fail = [](hipError_t e, const char* what) {
     return fail(SIFT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
   };
@@ -140,10 +180,9 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
       m.cap_a = q.cap_a;
       m.cap_b = q.cap_b;
       m.capacity = q.capacity;
-      m.rtiles = L.rtiles[first + t];
-      m.rowbest = L.rowbest[first + t];
-      m.colbest = L.colbest[first + t];
-      m.colpart = L.colpart[first + t];
+      m.best = L.best[first + t];
+      m.part = L.part[first + t];
+      m.half = L.half[first + t];
     }
     for (int t = 0; t <= c.count; ++t) {
       c.row_prefix[t] = rp[first + t];
@@ -153,8 +192,10 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   }
   if (rp[n] > 0 && (e = launch_match_rows(h, n, rp[n], stream)) != hipSuccess)
     return hip_fail(e, "match similarity");
-  if (cp[n] > 0 && (e = launch_match_cols(h, n, cp[n], stream)) != hipSuccess)
-    return hip_fail(e, "match columns");
+  if (L.merge && cp[n] > 0) {
+    if ((e = launch_match_cols(h, n, cp[n], stream)) != hipSuccess) return hip_fail(e, "match merge");
+    h.merged = 1;
+  }
   const float ratio_sq = (float)((double)ratio * (double)ratio);
   if ((e = launch_match_emit(h, n, ratio_sq, stream)) != hipSuccess) return hip_fail(e, "match emit");
   return SIFT_OK;

@@ -13,8 +13,10 @@
 namespace sift {
 
 constexpr int kMatchTile = 128;      // rows of either set per similarity tile
-constexpr int kMatchColBlock = 256;  // columns per block of the column reduction
+constexpr int kMatchOwnHalf = 256;    // own rows of a work-group where the sets are copied to fp16
+constexpr int kMatchMergeBlock = 256; // rows per block of the chunk merge
 constexpr int kMatchSetupChunk = 24; // pair-table entries per setup launch
+constexpr int kMatchMaxChunks = 8;   // most parts of a walk over the other set
 
 // Running nearest / second-nearest of one row or column: the best candidate
 // (largest value, smallest index among equals) and the largest value among
@@ -36,18 +38,23 @@ struct MatchEntry {
   int32_t* n_matches;
   int32_t* n_found;
   int32_t cap_a, cap_b, capacity;
-  int32_t rtiles;          // row tiles of kMatchTile rows that cap_a needs
-  int64_t rowbest;         // Top2 [cap_a]: a_i's nearest in b
-  int64_t colbest;         // Top2 [cap_b]: b_j's nearest in a
-  int64_t colpart;         // Top2 [cap_b][rtiles]: b_j's nearest within one row tile
+  int32_t pad;
+  int64_t best;            // Top2 [cap_a], then Top2 [cap_b]: a_i's nearest in b, b_j's in a
+  int64_t part;            // the same per chunk: Top2 [chunks][cap_a], then [chunks][cap_b]
+  int64_t half;            // fp16 copies of the sets: [cap_a][128], then [cap_b][128]
 };
 
 // Device addresses of the header arrays (computed on the host).
 struct MatchHdr {
   char* ws;
   const MatchEntry* table;   // [n]
-  int* row_prefix;           // [n + 1] row tiles before each pair
-  int* col_prefix;           // [n + 1] column blocks before each pair
+  int* row_prefix;           // [n + 1] row tiles (of both sets) before each pair
+  int* col_prefix;           // [n + 1] merge blocks (of both sets) before each pair
+  int chunks;                // parts every walk over the other set is cut into
+  int half;                  // 1: the sets are copied to fp16 first
+  int merged;                // 1: the chunks' results have been merged into `best`
+  int own_rows;              // rows per row tile of row_prefix: kMatchTile or kMatchOwnHalf
+  int same_tiles;            // row tiles of every pair when all have as many, else 0
 };
 
 struct MatchSetupChunk {
@@ -60,7 +67,9 @@ struct MatchSetupChunk {
 
 hipError_t launch_match_setup(const MatchHdr& h, const MatchSetupChunk& c, int n,
                               hipStream_t stream);
+// grid: row tiles of all pairs (row_prefix[n])
 hipError_t launch_match_rows(const MatchHdr& h, int n, int grid, hipStream_t stream);
+// merge of the chunks; grid: merge blocks of all pairs (col_prefix[n])
 hipError_t launch_match_cols(const MatchHdr& h, int n, int grid, hipStream_t stream);
 hipError_t launch_match_emit(const MatchHdr& h, int n, float ratio_sq, hipStream_t stream);
 

@@ -11,6 +11,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 #include "sift_device.h"
 #include "sift_match.h"
 
@@ -20,7 +22,7 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kMatchDim = 128;
-constexpr int kBStride = kMatchDim + 8;   // LDS row stride of the fp16 B tile (halves)
+constexpr int kTileStride = kMatchDim + 8;   // LDS row stride of an fp16 tile (halves)
 
 __device__ __forceinline__ Top2 top2_empty() {
   Top2 t;
@@ -33,16 +35,6 @@ __device__ __forceinline__ Top2 top2_empty() {
 
 __device__ __forceinline__ bool top2_better(float va, int ia, float vb, int ib) {
   return va > vb || (va == vb && ia < ib);
-}
-
-// Add (v, i) to t, for an index larger than every index pushed into t
-// before: a tie then keeps the earlier entry, so "better" is a strict
-// comparison of values, and a displaced first value is never below the second.
-__device__ __forceinline__ void top2_push_after(Top2& t, float v, int i) {
-  const bool up = v > t.v1;
-  t.v2 = up ? t.v1 : fmaxf(t.v2, v);
-  t.i1 = up ? i : t.i1;
-  t.v1 = up ? v : t.v1;
 }
 
 __device__ __forceinline__ Top2 top2_merge(const Top2& a, const Top2& b) {
@@ -99,164 +91,271 @@ __global__ void k_match_setup(MatchHdr h, MatchSetupChunk c, int n) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Similarity tiles.  One work-group (4 waves) per (pair, tile of 128 rows of
-// a); it walks the tiles of 128 rows of b.  Wave w covers a rows
-// 64 (w / 2) .. + 63 and b rows 64 (w % 2) .. + 63 of each tile as 4 x 4
-// blocks of 16 x 16, its a fragments held in registers for the whole walk and
-// the b tile staged in LDS as fp16.  Lane l supplies a row 16 ta + l % 16 and
-// b row 16 tb + l % 16, 8 values each at k = 32 kk + 8 (l / 16), and receives
-// s for a rows 16 ta + 4 (l / 16) + r, b row 16 tb + l % 16.
-//   rows:    every lane keeps the nearest b seen so far for its 16 a rows;
-//            at the end the 16 lanes of a row and the two waves of a row half
-//            are merged and written to rowbest.
-//   columns: per b tile, each lane summarises its 16 values of a b row, the
-//            four lane groups and the two waves holding that b row are
-//            merged, and the tile's summary goes to colpart[j][row tile].
-__global__ __launch_bounds__(256) void k_match_rows(MatchHdr h, int n) {
-  __shared__ __align__(16) _Float16 s_b[kMatchTile * kBStride];
-  __shared__ Top2 s_part[2][kMatchTile];
-  const int item = blockIdx.x;
-  const int p = find_owner(h.row_prefix, n, item);
-  const int rt = item - h.row_prefix[p];
+// Where the results of set `b_side` (0: a, 1: b) of a pair lie.
+__device__ __forceinline__ Top2* best_of(const MatchHdr& h, const MatchEntry& e, int b_side) {
+  return reinterpret_cast<Top2*>(h.ws + e.best) + (b_side ? e.cap_a : 0);
+}
+__device__ __forceinline__ Top2* part_of(const MatchHdr& h, const MatchEntry& e, int b_side,
+                                         int chunk) {
+  return reinterpret_cast<Top2*>(h.ws + e.part) +
+         (b_side ? (int64_t)h.chunks * e.cap_a + (int64_t)chunk * e.cap_b
+                 : (int64_t)chunk * e.cap_a);
+}
+__device__ __forceinline__ _Float16* half_of(const MatchHdr& h, const MatchEntry& e, int b_side) {
+  return reinterpret_cast<_Float16*>(h.ws + e.half) + (b_side ? (int64_t)e.cap_a * kMatchDim : 0);
+}
+
+// Pair of a row tile and the tile's number within it.  Pairs of equal tile
+// counts need no search: its dependent loads were a third of a work-group's time
+// before its first product.
+__device__ __forceinline__ int pair_of_tile(const MatchHdr& h, int n, int tile, int* local) {
+  if (h.same_tiles) {
+    const int p = tile / h.same_tiles;
+    *local = tile - p * h.same_tiles;
+    return p;
+  }
+  const int p = __builtin_amdgcn_readfirstlane(find_owner(h.row_prefix, n, tile));
+  *local = tile - __builtin_amdgcn_readfirstlane(h.row_prefix[p]);
+  return p;
+}
+
+// The sets as fp16 (round to nearest even), one work-group per row tile.
+__global__ __launch_bounds__(256) void k_match_half(MatchHdr h, int n) {
+  int local;
+  const int p = pair_of_tile(h, n, blockIdx.x, &local);
   const MatchEntry e = h.table[p];
-  const int na = rows_in_use(e.count_a, e.cap_a);
-  const int nb = rows_in_use(e.count_b, e.cap_b);
-  const int row0 = rt * kMatchTile;
-  if (row0 >= na) return;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int li = lane & 15, gq = lane >> 4;
-  const int ahalf = wv >> 1, bhalf = wv & 1;
-  Top2* rowbest = reinterpret_cast<Top2*>(h.ws + e.rowbest);
-  Top2* colpart = reinterpret_cast<Top2*>(h.ws + e.colpart);
-
-  // a fragments: row row0 + 64 ahalf + 16 ta + li, k = 32 kk + 8 gq
-  half8 fa[4][4];
-#pragma unroll
-  for (int ta = 0; ta < 4; ++ta) {
-    const int ia = row0 + 64 * ahalf + 16 * ta + li;
-    const float* arow = e.desc_a + (int64_t)(ia < na ? ia : 0) * kMatchDim;
-    SIFT_CHECK_INDEX(ia < na ? ia : 0, e.cap_a);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fa[ta][kk] = load_half8(arow, 32 * kk + 8 * gq, ia < na);
-  }
-  Top2 rs[4][4];   // [ta][r]: a row row0 + 64 ahalf + 16 ta + 4 gq + r
-#pragma unroll
-  for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) rs[ta][r] = top2_empty();
-
-  const int ctiles = (nb + kMatchTile - 1) / kMatchTile;
-  for (int ct = 0; ct < ctiles; ++ct) {
-    const int col0 = ct * kMatchTile;
-    __syncthreads();   // the previous tile's LDS reads are done
-    {
-      // b tile into LDS as fp16: thread t converts 64 values of row t / 2
-      const int jr = t >> 1, k0 = 64 * (t & 1);
-      const int jb = col0 + jr;
-      const float* brow = e.desc_b + (int64_t)(jb < nb ? jb : 0) * kMatchDim;
-      SIFT_CHECK_INDEX(jb < nb ? jb : 0, e.cap_b);
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        *reinterpret_cast<half8*>(&s_b[jr * kBStride + k0 + 8 * q]) =
-            load_half8(brow, k0 + 8 * q, jb < nb);
+  const int at = (e.cap_a + h.own_rows - 1) / h.own_rows;
+  const int b_side = local >= at;
+  const int row0 = (b_side ? local - at : local) * h.own_rows;
+  const int rows = b_side ? rows_in_use(e.count_b, e.cap_b) : rows_in_use(e.count_a, e.cap_a);
+  const float* src = b_side ? e.desc_b : e.desc_a;
+  _Float16* dst = half_of(h, e, b_side);
+  for (int i = 0; i < h.own_rows * (kMatchDim / 8) / 256; ++i) {
+    const int piece = i * 256 + threadIdx.x;
+    const int row = row0 + piece / (kMatchDim / 8), k = piece % (kMatchDim / 8) * 8;
+    if (row < rows) {
+      SIFT_CHECK_INDEX(row, b_side ? e.cap_b : e.cap_a);
+      *reinterpret_cast<half8*>(dst + (int64_t)row * kMatchDim + k) =
+          load_half8(src + (int64_t)row * kMatchDim, k, true);
     }
-    __syncthreads();
-    float4v acc[4][4];
-#pragma unroll
-    for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-      for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      half8 fb[4];
-#pragma unroll
-      for (int tb = 0; tb < 4; ++tb)
-        fb[tb] = *reinterpret_cast<const half8*>(
-            &s_b[(64 * bhalf + 16 * tb + li) * kBStride + 32 * kk + 8 * gq]);
-#pragma unroll
-      for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
-          acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[ta][kk], fb[tb], acc[ta][tb],
-                                                               0, 0, 0);
-    }
-    // rows: this lane's b row of each block (a lane's b rows come in
-    // increasing order, over tb and over tiles)
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb) {
-      const int jb = col0 + 64 * bhalf + 16 * tb + li;
-      if (jb < nb) {
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) top2_push_after(rs[ta][r], acc[ta][tb][r], jb);
-      }
-    }
-    // columns: b row 16 tb + li over this wave's 64 a rows (in increasing
-    // order over ta and r)
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb) {
-      Top2 c = top2_empty();
-#pragma unroll
-      for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int ia = row0 + 64 * ahalf + 16 * ta + 4 * gq + r;
-          if (ia < na) top2_push_after(c, acc[ta][tb][r], ia);
-        }
-      c = top2_merge(c, top2_shfl_xor(c, 16));
-      c = top2_merge(c, top2_shfl_xor(c, 32));
-      if (gq == 0) s_part[ahalf][64 * bhalf + 16 * tb + li] = c;
-    }
-    __syncthreads();
-    if (t < kMatchTile && col0 + t < nb) {
-      SIFT_CHECK_INDEX((int64_t)(col0 + t) * e.rtiles + rt, (int64_t)e.cap_b * e.rtiles);
-      colpart[(int64_t)(col0 + t) * e.rtiles + rt] = top2_merge(s_part[0][t], s_part[1][t]);
-    }
-  }
-  // rows: merge the 16 lanes of each row, then the two b halves
-#pragma unroll
-  for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      Top2 v = rs[ta][r];
-#pragma unroll
-      for (int m = 1; m < 16; m <<= 1) v = top2_merge(v, top2_shfl_xor(v, m));
-      rs[ta][r] = v;
-    }
-  __syncthreads();
-  if (li == 0) {
-#pragma unroll
-    for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) s_part[bhalf][64 * ahalf + 16 * ta + 4 * gq + r] = rs[ta][r];
-  }
-  __syncthreads();
-  if (t < kMatchTile && row0 + t < na) {
-    SIFT_CHECK_INDEX(row0 + t, e.cap_a);
-    rowbest[row0 + t] = top2_merge(s_part[0][t], s_part[1][t]);
   }
 }
 
-// b_j's nearest in a: merge of its per-row-tile summaries (one thread per j).
-__global__ __launch_bounds__(kMatchColBlock) void k_match_cols(MatchHdr h, int n) {
-  const int item = blockIdx.x;
-  const int p = find_owner(h.col_prefix, n, item);
-  const int j = (item - h.col_prefix[p]) * kMatchColBlock + threadIdx.x;
+// ---------------------------------------------------------------------------
+// Nearest neighbours.  One work-group (4 waves) per (pair, set, tile of 32 OB
+// rows of that set, its own rows, chunk of the other set); it walks the chunk's
+// tiles of 128 rows.  Waves 2 h and 2 h + 1 hold half h of the own rows as
+// MFMA B operands in registers for the whole walk and take the two halves of
+// each tile, which is staged in LDS as fp16 (two buffers: the next tile is on
+// its way while the current one is computed).  Lane l supplies other row
+// 16 ta + l % 16 and own row 16 tb + l % 16, 8 values each at k = 32 kk + 8
+// (l / 16), and receives s for other rows 16 ta + 4 (l / 16) + r, own row
+// 16 tb + l % 16: every value a lane receives belongs to one of OB own rows,
+// whose nearest and second nearest it keeps.  Both directions are walked this
+// way: the products are computed twice, on matrix cores that would idle
+// otherwise, and no summary leaves the lane before the end of the walk.
+//
+// Bound: matrix products and vector issue in turn (four operations per
+// similarity: comparison, second largest as a median, two selects), with what is
+// read from LDS on top; of 83 us for 32 pairs of 2000 x 2000 the products take 30,
+// the comparisons 18.  Keeping both directions' summaries from one product took 20
+// states per lane, merges between lanes per tile, and tiles converted between
+// two barriers: 236 us, and 398 us for one pair of 8192 x 7900 (now 50), whose 64
+// row tiles left three quarters of the chip idle.
+// HALF: the sets have been copied to fp16.  OB: blocks of 16 own rows per wave.
+// Eight read half of LDS and memory per product that four do (83 against 96
+// us), four make twice the work-groups of a small call.
+template <bool HALF, int OB>
+__global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int tiles) {
+  // HALF: a tile is copied to LDS by the load unit, rows unpadded, the 16-byte
+  // pieces of row r at places p ^ (r % 16) (the 16 rows a wave reads together
+  // then lie in different banks)
+  constexpr int kStride = HALF ? kMatchDim : kTileStride;
+  __shared__ __align__(256) _Float16 s_t0[kMatchTile * kStride], s_t1[kMatchTile * kStride];
+  constexpr int kOwn = 32 * OB;   // own rows of the work-group
+  __shared__ Top2 s_part[2][kOwn];
+  // neighbouring items (one pair's tiles) to one XCD, whose L2 then holds the pair
+  const int per_xcd = gridDim.x / kXcds;
+  const int item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+  if (item >= tiles * h.chunks) return;
+  const int chunk = item % h.chunks, tile = item / h.chunks;
+  int local;
+  const int p = pair_of_tile(h, n, tile, &local);
   const MatchEntry e = h.table[p];
-  const int na = rows_in_use(e.count_a, e.cap_a);
-  const int nb = rows_in_use(e.count_b, e.cap_b);
-  if (j >= nb) return;
-  const Top2* colpart = reinterpret_cast<const Top2*>(h.ws + e.colpart);
-  Top2 c = top2_empty();
-  const int used = (na + kMatchTile - 1) / kMatchTile;
-  for (int rt = 0; rt < used; ++rt) {
-    SIFT_CHECK_INDEX((int64_t)j * e.rtiles + rt, (int64_t)e.cap_b * e.rtiles);
-    c = top2_merge(c, colpart[(int64_t)j * e.rtiles + rt]);
+  const int at = (e.cap_a + kOwn - 1) / kOwn;
+  const int b_side = local >= at;   // own rows are b's
+  const int row0 = (b_side ? local - at : local) * kOwn;
+  const int na = __builtin_amdgcn_readfirstlane(rows_in_use(e.count_a, e.cap_a));
+  const int nb = __builtin_amdgcn_readfirstlane(rows_in_use(e.count_b, e.cap_b));
+  const int n_own = b_side ? nb : na, n_oth = b_side ? na : nb;
+  if (row0 >= n_own) return;
+  const int cap_own = b_side ? e.cap_b : e.cap_a, cap_oth = b_side ? e.cap_a : e.cap_b;
+  const float* f_own = b_side ? e.desc_b : e.desc_a;
+  const float* f_oth = b_side ? e.desc_a : e.desc_b;
+  const _Float16* h_own = HALF ? half_of(h, e, b_side) : nullptr;
+  const _Float16* h_oth = HALF ? half_of(h, e, !b_side) : nullptr;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int li = lane & 15, gq = lane >> 4;
+  const int own_half = wv >> 1, oth_half = wv & 1;
+  // 8 values of a row as fp16
+  auto piece_of = [&](const _Float16* hs, const float* fs, int64_t at) {
+    if (HALF) return *reinterpret_cast<const half8*>(hs + at);
+    return load_half8(fs + at, 0, true);
+  };
+  // own fragments: row row0 + 64 own_half + 16 tb + li, k = 32 kk + 8 gq (rows past
+  // the set's end repeat the last one; nothing of theirs is stored)
+  half8 fb[OB][4];
+#pragma unroll
+  for (int tb = 0; tb < OB; ++tb) {
+    const int i = min(row0 + 16 * OB * own_half + 16 * tb + li, n_own - 1);
+    SIFT_CHECK_INDEX(i, cap_own);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      fb[tb][kk] = piece_of(h_own, f_own, (int64_t)i * kMatchDim + 32 * kk + 8 * gq);
   }
-  SIFT_CHECK_INDEX(j, e.cap_b);
-  reinterpret_cast<Top2*>(h.ws + e.colbest)[j] = c;
+  float v1[OB], v2[OB];
+  int i1[OB];
+#pragma unroll
+  for (int tb = 0; tb < OB; ++tb) {
+    v1[tb] = v2[tb] = -INFINITY;
+    i1[tb] = 0x7fffffff;
+  }
+  // pieces of 8 values of a tile: 8 per thread, piece i of thread t in row
+  // 16 i + t / 16 (rows past the set's end repeat the last one: the walk leaves
+  // them out)
+  constexpr int kPieces = kMatchTile * kMatchDim / 8 / 256, kPieceRows = kMatchTile / kPieces;
+  static_assert(kPieceRows * (kMatchDim / 8) == 256, "a piece of every thread is whole rows");
+  const int prow = t / (kMatchDim / 8), pk = t % (kMatchDim / 8) * 8;
+  auto stage = [&](int ct, _Float16* buf) {
+    const int r0 = ct * kMatchTile;
+    if constexpr (HALF) {
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const int row = min(r0 + kPieceRows * i + prow, n_oth - 1);
+        SIFT_CHECK_INDEX(row, cap_oth);
+        const _Float16* from = h_oth + (int64_t)row * kMatchDim + (pk ^ (prow * 8));
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)from,
+            (__attribute__((address_space(3))) void*)(buf + (256 * i + 64 * wv) * 8), 16, 0, 0);
+      }
+    } else {
+      half8 st[kPieces];
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const int row = min(r0 + kPieceRows * i + prow, n_oth - 1);
+        SIFT_CHECK_INDEX(row, cap_oth);
+        st[i] = load_half8(f_oth + (int64_t)row * kMatchDim, pk, true);
+      }
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i)
+        *reinterpret_cast<half8*>(&buf[(kPieceRows * i + prow) * kStride + pk]) = st[i];
+    }
+  };
+  // the chunk's tiles of the other set, from the rows in use
+  const int used = (n_oth + kMatchTile - 1) / kMatchTile;
+  const int c0 = used * chunk / h.chunks, c1 = used * (chunk + 1) / h.chunks;
+  // one tile: TAIL, the last one, has rows past the set's end
+  auto walk = [&](auto tail, const _Float16* buf, int ct) {
+    constexpr bool TAIL = decltype(tail)::value;
+    const int o0 = ct * kMatchTile + 64 * oth_half + 4 * gq;   // the lane's other row at ta = r = 0
+    int code[OB];   // 4 ta + r of the new nearest
+#pragma unroll
+    for (int tb = 0; tb < OB; ++tb) code[tb] = -1;
+    auto products = [&](int ta, float4v* acc) {
+#pragma unroll
+      for (int tb = 0; tb < OB; ++tb) acc[tb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const half8 fa = *reinterpret_cast<const half8*>(
+            &buf[(64 * oth_half + 16 * ta + li) * kStride +
+                 (HALF ? (32 * kk + 8 * gq) ^ (8 * li) : 32 * kk + 8 * gq)]);
+#pragma unroll
+        for (int tb = 0; tb < OB; ++tb)
+          acc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa, fb[tb][kk], acc[tb], 0, 0, 0);
+      }
+    };
+    float4v acc[OB];
+#pragma unroll
+    for (int ta = 0; ta < 4; ++ta) {
+      products(ta, acc);
+      // A lane meets its other rows in increasing order, so a tie keeps the
+      // earlier one: "nearer" is a strict comparison.  v2 <= v1: the second
+      // largest of the three is their median.
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int tb = 0; tb < OB; ++tb) {
+          float s = acc[tb][r];
+          if (TAIL) s = o0 + 16 * ta + r < n_oth ? s : -INFINITY;
+          const bool up = s > v1[tb];
+          code[tb] = up ? 4 * ta + r : code[tb];
+          v2[tb] = __builtin_amdgcn_fmed3f(v1[tb], v2[tb], s);
+          v1[tb] = up ? s : v1[tb];
+        }
+      // One block's comparisons end here and one block's products are in flight,
+      // no more: left alone, the compiler keeps all 64 values and takes 256
+      // registers.
+#pragma unroll
+      for (int tb = 0; tb < OB; ++tb)
+        __asm__ volatile("" : "+v"(v1[tb]), "+v"(v2[tb]), "+v"(code[tb]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int tb = 0; tb < OB; ++tb)
+      i1[tb] = code[tb] >= 0 ? o0 + 16 * (code[tb] >> 2) + (code[tb] & 3) : i1[tb];
+  };
+  auto step = [&](int ct, const _Float16* buf, _Float16* next) {
+    if (ct + 1 < c1) stage(ct + 1, next);
+    if ((ct + 1) * kMatchTile > n_oth)
+      walk(std::true_type(), buf, ct);
+    else
+      walk(std::false_type(), buf, ct);
+    __syncthreads();
+  };
+  if (c0 < c1) stage(c0, s_t0);
+  __syncthreads();
+  for (int ct = c0; ct < c1; ct += 2) {
+    step(ct, s_t0, s_t1);
+    if (ct + 1 < c1) step(ct + 1, s_t1, s_t0);
+  }
+  // merge the four lanes of an own row, then the two halves of the tiles
+#pragma unroll
+  for (int tb = 0; tb < OB; ++tb) {
+    Top2 v;
+    v.v1 = v1[tb];
+    v.i1 = i1[tb];
+    v.v2 = v2[tb];
+    v.pad = 0;
+    v = top2_merge(v, top2_shfl_xor(v, 16));
+    v = top2_merge(v, top2_shfl_xor(v, 32));
+    if (gq == 0) s_part[oth_half][16 * OB * own_half + 16 * tb + li] = v;
+  }
+  __syncthreads();
+  if (t < kOwn && row0 + t < n_own) {
+    SIFT_CHECK_INDEX(row0 + t, cap_own);
+    Top2* out = h.chunks == 1 ? best_of(h, e, b_side) : part_of(h, e, b_side, chunk);
+    out[row0 + t] = top2_merge(s_part[0][t], s_part[1][t]);
+  }
+}
+
+// The nearest over all chunks of row i of one set.
+__device__ __forceinline__ Top2 best_at(const MatchHdr& h, const MatchEntry& e, int b_side, int i) {
+  if (h.chunks == 1 || h.merged) return best_of(h, e, b_side)[i];
+  Top2 c = part_of(h, e, b_side, 0)[i];
+  for (int q = 1; q < h.chunks; ++q) c = top2_merge(c, part_of(h, e, b_side, q)[i]);
+  return c;
+}
+
+// Merge of the chunks, one thread per row of either set.
+__global__ __launch_bounds__(kMatchMergeBlock) void k_match_merge(MatchHdr h, int n) {
+  const int p = find_owner(h.col_prefix, n, blockIdx.x);
+  const MatchEntry e = h.table[p];
+  int i = (blockIdx.x - h.col_prefix[p]) * kMatchMergeBlock + threadIdx.x;
+  const int b_side = i >= e.cap_a;
+  if (b_side) i -= e.cap_a;
+  if (i >= (b_side ? rows_in_use(e.count_b, e.cap_b) : rows_in_use(e.count_a, e.cap_a))) return;
+  SIFT_CHECK_INDEX(i, b_side ? e.cap_b : e.cap_a);
+  best_of(h, e, b_side)[i] = best_at(h, e, b_side, i);
 }
 
 // Squared distance of unit vectors from a similarity, in fp32.
@@ -269,44 +368,76 @@ __device__ __forceinline__ bool ratio_pass(const Top2& t, float ratio_sq) {
 }
 
 // Mutual nearest neighbours passing both ratio tests, written in ascending
-// query order (one work-group per pair, a block scan per 256 rows).
-__global__ __launch_bounds__(256) void k_match_emit(MatchHdr h, int n, float ratio_sq) {
-  __shared__ int s_wave[4];
+// query order (one work-group per pair).  Up to kEmitRows x 1024 rows are taken
+// together: their loads are all in flight at once, and one scan of the waves'
+// counts places them (a scan per 256 rows took 36 us for 8192 rows).
+constexpr int kEmitThreads = 1024, kEmitRows = 8;
+
+__global__ __launch_bounds__(kEmitThreads) void k_match_emit(MatchHdr h, int n, float ratio_sq) {
+  constexpr int kCounts = kEmitRows * kEmitThreads / 64;   // one per 64 rows
+  __shared__ int s_cnt[kCounts], s_wave[4];
   const MatchEntry e = h.table[blockIdx.x];
   const int na = rows_in_use(e.count_a, e.cap_a);
   const int nb = rows_in_use(e.count_b, e.cap_b);
-  const Top2* rowbest = reinterpret_cast<const Top2*>(h.ws + e.rowbest);
-  const Top2* colbest = reinterpret_cast<const Top2*>(h.ws + e.colbest);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int base = 0;
   const int rows = nb > 0 ? na : 0;
-  for (int i0 = 0; i0 < rows; i0 += 256) {
-    const int i = i0 + threadIdx.x;
-    bool keep = false;
-    Top2 rb = top2_empty();
-    if (i < rows) {
-      SIFT_CHECK_INDEX(i, e.cap_a);
-      rb = rowbest[i];
-      const int j = rb.i1;
-      if (j >= 0 && j < nb) {
-        SIFT_CHECK_INDEX(j, e.cap_b);
-        const Top2 cb = colbest[j];
-        keep = cb.i1 == i && ratio_pass(rb, ratio_sq) && ratio_pass(cb, ratio_sq);
+  for (int i0 = 0; i0 < rows; i0 += kEmitRows * kEmitThreads) {
+    Top2 rb[kEmitRows];
+    unsigned long long kept[kEmitRows];
+#pragma unroll
+    for (int u = 0; u < kEmitRows; ++u) {
+      const int i = i0 + u * kEmitThreads + t;
+      rb[u] = top2_empty();
+      if (i < rows) {
+        SIFT_CHECK_INDEX(i, e.cap_a);
+        rb[u] = best_at(h, e, 0, i);
       }
     }
-    int tot;
-    const int ex = block_excl_scan256(keep ? 1 : 0, s_wave, &tot);
-    if (keep && base + ex < e.capacity) {
-      sift_match m;
-      m.query = i;
-      m.train = rb.i1;
-      m.similarity = rb.v1;
-      m.distance = sqrtf(sq_dist(rb.v1));
-      SIFT_CHECK_INDEX(base + ex, e.capacity);
-      e.matches[base + ex] = m;
+#pragma unroll
+    for (int u = 0; u < kEmitRows; ++u) {
+      const int i = i0 + u * kEmitThreads + t, j = rb[u].i1;
+      bool keep = false;
+      if (i < rows && j >= 0 && j < nb) {
+        SIFT_CHECK_INDEX(j, e.cap_b);
+        const Top2 cb = best_at(h, e, 1, j);
+        keep = cb.i1 == i && ratio_pass(rb[u], ratio_sq) && ratio_pass(cb, ratio_sq);
+      }
+      kept[u] = __ballot(keep);
+      if (lane == 0) s_cnt[u * (kEmitThreads / 64) + wave] = __popcll(kept[u]);
     }
-    base += tot;
+    __syncthreads();
+    // exclusive prefix of the counts (in row order), by the first two waves
+    int c = t < kCounts ? s_cnt[t] : 0;
+    const int incl = wave_incl_scan(c);
+    if (t < kCounts && lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = 0, sum = 0;
+#pragma unroll
+    for (int w = 0; w < kCounts / 64; ++w) {
+      if (w < wave) before += s_wave[w];
+      sum += s_wave[w];
+    }
+    if (t < kCounts) s_cnt[t] = before + incl - c;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEmitRows; ++u) {
+      const int at = base + s_cnt[u * (kEmitThreads / 64) + wave] +
+                     __popcll(kept[u] & lanemask_lt());
+      if ((kept[u] >> lane & 1ull) && at < e.capacity) {
+        sift_match m;
+        m.query = i0 + u * kEmitThreads + t;
+        m.train = rb[u].i1;
+        m.similarity = rb[u].v1;
+        m.distance = sqrtf(sq_dist(rb[u].v1));
+        SIFT_CHECK_INDEX(at, e.capacity);
+        e.matches[at] = m;
+      }
+    }
+    base += sum;
+    __syncthreads();   // the counts are read before the next rows' are written
   }
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     *e.n_matches = base < e.capacity ? base : e.capacity;
     if (e.n_found) *e.n_found = base;
   }
@@ -318,15 +449,21 @@ hipError_t launch_match_setup(const MatchHdr& h, const MatchSetupChunk& c, int n
 }
 
 hipError_t launch_match_rows(const MatchHdr& h, int n, int grid, hipStream_t stream) {
-  return launch(k_match_rows, dim3(grid), dim3(256), stream, h, n);
+  if (h.half) {
+    const hipError_t e = launch(k_match_half, dim3(grid), dim3(256), stream, h, n);
+    if (e != hipSuccess) return e;
+  }
+  const int items = (grid * h.chunks + kXcds - 1) / kXcds * kXcds;
+  return launch(h.half ? k_match_best<true, kMatchOwnHalf / 32> : k_match_best<false, kMatchTile / 32>,
+                dim3(items), dim3(256), stream, h, n, grid);
 }
 
 hipError_t launch_match_cols(const MatchHdr& h, int n, int grid, hipStream_t stream) {
-  return launch(k_match_cols, dim3(grid), dim3(kMatchColBlock), stream, h, n);
+  return launch(k_match_merge, dim3(grid), dim3(kMatchMergeBlock), stream, h, n);
 }
 
 hipError_t launch_match_emit(const MatchHdr& h, int n, float ratio_sq, hipStream_t stream) {
-  return launch(k_match_emit, dim3(n), dim3(256), stream, h, n, ratio_sq);
+  return launch(k_match_emit, dim3(n), dim3(kEmitThreads), stream, h, n, ratio_sq);
 }
 
 // The bounds-check counter of this file's kernels (see check_index).
