@@ -110,7 +110,8 @@ typedef struct {
   int32_t blur_chain;         /* 0: library choice (2); 1: one launch per Gaussian level; 2..4: up
                                  to that many consecutive levels of an octave blurred in one
                                  launch (runs of radius <= 8 that the library has a kernel
-                                 for), so the levels between are not read back from memory.
+                                 for), so the levels between are not read back from memory;
+                                 0 and 2 also take octaves of few pixels whole in one launch.
                                  Any value gives bit-identical results (tuning only) */
   int32_t detect_waves;       /* 0: library choice (4); 4 or 8: waves per work-group of the
                                  extrema search, which share a band's column segments.

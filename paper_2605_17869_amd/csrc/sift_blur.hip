@@ -549,6 +549,182 @@ __global__ __launch_bounds__(kBlurThreads, 2) void k_chain(ChainArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// A whole octave in one launch, for octaves of so few pixels that a launch's
+// time is the time of one work-group: per tile of TX x 32 pixels one work-group
+// loads the source region that all levels together reach (radii 5, 7, 8, 10, 13:
+// 43 pixels on every side) and blurs it level after level in LDS, each level's
+// region smaller by its radius.  The tile's pixels of every level are stored.  The
+// pixels beyond an image border come from mirrored source data and, by the tap
+// order of gauss_pairs, equal the mirrored values bit for bit; every value is the
+// one the other kernels compute.
+//
+// A pass takes 8 outputs per task from a window of 8 + 2 R values: vertically
+// with neighbouring lanes on neighbouring columns, horizontally on neighbouring
+// rows of odd pitch, both without bank conflicts.
+//
+// Bound: latency.  The region costs 5 times the operations of separate launches
+// (7 us of a CU's vector issue per 32 x 32 tile), which an idle chip has to spare:
+// a later octave takes 19 us instead of 44 in four launches of 8 to 17 us.  A tile
+// needs a CU's LDS to itself, so a launch is worth one round of tiles; wider
+// tiles (30 us instead of 24) hold the first octave of a 640x480 image to one.
+template <int TX, int... Rs>
+struct OctGeom {
+  static constexpr int N = sizeof...(Rs);
+  static constexpr int r(int i) {
+    constexpr int v[] = {Rs...};
+    return v[i];
+  }
+  // pixels that level i is computed beyond the tile
+  static constexpr int halo(int i) {
+    int s = 0;
+    for (int j = i + 1; j < N; ++j) s += r(j);
+    return s;
+  }
+  static constexpr int cols(int i) { return TX + 2 * halo(i); }   // of level i's region
+  static constexpr int rows(int i) { return kOctTileH + 2 * halo(i); }
+  static constexpr int src_halo() { return halo(0) + r(0); }
+  static constexpr int src_cols() { return TX + 2 * src_halo(); }
+  static constexpr int src_rows() { return kOctTileH + 2 * src_halo(); }
+};
+
+constexpr int kOctThreads = 1024;
+constexpr int kOctRun = 8;   // outputs per task
+
+template <int TX, int MODE, int ST, int... Rs>
+__global__ __launch_bounds__(kOctThreads) void k_octave(ChainArgs a) {
+  using Geo = OctGeom<TX, Rs...>;
+  constexpr int N = Geo::N, TY = kOctTileH, RUN = kOctRun, NT = kOctThreads;
+  constexpr bool UP = MODE == kSrcUpsample;
+  constexpr bool D16 = ST >= 1;
+  constexpr uint32_t ES_D = D16 ? 2u : 4u;
+  constexpr int SC = Geo::src_cols(), SR = Geo::src_rows();
+  constexpr int P = SC | 1;                 // row pitch: odd
+  static_assert(N <= kOctMaxLevels, "levels");
+  // s_a: a level (first the source); s_b: its vertical pass.  Runs past a
+  // region's last row or column read up to RUN - 1 rows or values more.
+  __shared__ float s_a[(SR + RUN) * P], s_b[(Geo::rows(0) + RUN) * P + RUN];
+
+  // the image and tile of this work-group: lane i holds image i's tiles
+  const int t = threadIdx.x, lane = t & 63;
+  int img, local;
+  {
+    int hk = 0, wk = 0;
+    if (lane < a.n) octave_dims(a.table[lane].h, a.table[lane].w, a.p.upsample, a.k, &hk, &wk);
+    const int tiles = cdiv(wk, TX) * cdiv(hk, TY);
+    const int incl = wave_incl_scan(tiles);
+    const uint64_t past = __ballot(incl > (int)blockIdx.x);
+    if (past == 0ull) return;   // a grid sized for larger images than the table's
+    img = __builtin_ctzll(past);
+    local = blockIdx.x - (__builtin_amdgcn_readlane(incl, img) - __builtin_amdgcn_readlane(tiles, img));
+  }
+  const ImgEntry e = a.table[img];
+  const LayoutCfg lc = layout_cfg(a.p);
+  const int k = a.k;
+  const OctView ov = octave_view(e.h, e.w, lc, k);
+  const int hk = ov.h, wk = ov.w;
+  const int across = cdiv(wk, TX);
+  const int ty = local / across;
+  const int x0 = (local - ty * across) * TX, y0 = ty * TY;
+  const int64_t pkb = ES_D * (int64_t)ov.pitch;
+  SIFT_SPAN(rs, region_span(a.ws, e, lc));
+
+  // the source region: a wave takes 64 columns of a row at a time
+  {
+    constexpr int CW = (SC + 63) / 64;              // waves along a row
+    constexpr int ROWS = NT / 64 / CW;              // rows in flight
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int c = (wave % CW) * 64 + lane;
+    const int xs = x0 - Geo::src_halo() + min(c, SC - 1);
+    BlurSource<UP, ST> src;
+    src.init(a.ws, e, lc, ov, k, a.lv0, MODE, a.p.s, mirror(xs, wk));
+    const int g = wave / CW;
+    constexpr int LOADS = (SR + ROWS - 1) / ROWS;
+    if (g < ROWS) {
+      float v[LOADS];   // all of a thread's loads are in flight together
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i)
+        v[i] = src.fetch(mirror(y0 - Geo::src_halo() + min(g + i * ROWS, SR - 1), hk));
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i) {
+        const int r = g + i * ROWS;
+        if (r < SR && c < SC) {
+          SIFT_CHECK_INDEX(r * P + c, SR * P);
+          s_a[r * P + c] = v[i];
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  // the tile's pixels of the level in s_a (halo h around them)
+  auto store = [&](int level, int h) {
+    gchar* dst = uniform_ptr(reinterpret_cast<gchar*>(as_global(level_ptr(a.ws, e, ov, level))));
+#pragma unroll
+    for (int i = t; i < TX * TY; i += NT) {
+      const int py = i / TX, px = i - (i / TX) * TX;
+      if (y0 + py < hk && x0 + px < wk) {
+        gchar* row = dst + (y0 + py) * pkb;
+        SIFT_CHECK_IN(rs, row + (uint32_t)(x0 + px) * ES_D, ES_D);
+        store_lv<D16>(row, (uint32_t)(x0 + px) * ES_D, s_a[(h + py) * P + h + px]);
+      }
+    }
+  };
+  auto level = [&](auto i_c) {
+    constexpr int I = decltype(i_c)::value;
+    constexpr int R = Geo::r(I);
+    constexpr int J = I == 0 ? 0 : I - 1;
+    constexpr int CI = I == 0 ? SC : Geo::cols(J);              // columns read
+    constexpr int CO = Geo::cols(I), RO = Geo::rows(I);        // columns and rows written
+    static_assert(CI == CO + 2 * R, "a level's region shrinks by its radius");
+    constexpr int VSEGS = (RO + RUN - 1) / RUN, HSEGS = (CO + RUN - 1) / RUN;
+    auto gt = [&](int q) { return a.g[I][q]; };
+    // what s_a holds is stored while it is read
+    if (I > 0) store(a.lv0 + J, Geo::halo(J));
+    if (I == 0 && MODE == kSrcDown) store(0, Geo::src_halo());
+    // vertical pass: column x, rows 8 seg .. + 7 of the output
+    for (int task = t; task < CI * VSEGS; task += NT) {
+      const int seg = task / CI, x = task - (task / CI) * CI;
+      const float* in = &s_a[seg * RUN * P + x];
+      SIFT_CHECK_INDEX((seg * RUN + RUN + 2 * R - 1) * P + x, (SR + RUN) * P);
+      float w[RUN + 2 * R];
+#pragma unroll
+      for (int j = 0; j < RUN + 2 * R; ++j) w[j] = in[j * P];
+      float* out = &s_b[seg * RUN * P + x];
+      SIFT_CHECK_INDEX((seg * RUN + RUN - 1) * P + x, (Geo::rows(0) + RUN) * P + RUN);
+#pragma unroll
+      for (int q = 0; q < RUN; ++q) out[q * P] = gauss_pairs<R>(gt, [&](int j) { return w[q + j]; });
+    }
+    __syncthreads();
+    // horizontal pass: row y, columns 8 seg .. + 7 of the output
+    for (int task = t; task < RO * HSEGS; task += NT) {
+      const int seg = task / RO, y = task - (task / RO) * RO;
+      const float* in = &s_b[y * P + seg * RUN];
+      SIFT_CHECK_INDEX(y * P + seg * RUN + RUN + 2 * R - 1, (Geo::rows(0) + RUN) * P + RUN);
+      float w[RUN + 2 * R];
+#pragma unroll
+      for (int j = 0; j < RUN + 2 * R; ++j) w[j] = in[j];
+      float* out = &s_a[y * P + seg * RUN];
+      SIFT_CHECK_INDEX(y * P + seg * RUN + RUN - 1, (SR + RUN) * P);
+#pragma unroll
+      for (int q = 0; q < RUN; ++q) {
+        const float v = gauss_pairs<R>(gt, [&](int j) { return w[q + j]; });
+        // the next level reads the stored value; a run's end past the region
+        // would fall into the next row
+        if (seg * RUN + q < CO) out[q] = D16 ? round_f16(v) : v;
+      }
+    }
+    __syncthreads();
+  };
+  level(std::integral_constant<int, 0>());
+  level(std::integral_constant<int, 1>());
+  level(std::integral_constant<int, 2>());
+  level(std::integral_constant<int, 3>());
+  level(std::integral_constant<int, 4>());
+  if constexpr (N > 5) level(std::integral_constant<int, 5>());
+  store(a.lv0 + N - 1, 0);
+}
+
+// ---------------------------------------------------------------------------
 // Launch helpers
 
 typedef void (*BlurKernel)(BlurArgs);
@@ -586,13 +762,21 @@ hipError_t launch_blur(const BlurArgs& a, int radius, int grid, hipStream_t stre
 // their prefixes and the runs that start inside an octave.
 typedef void (*ChainKernel)(ChainArgs);
 struct ChainEntry {
-  int mode, st, n, r[kChainMaxLevels];
+  int mode, st, n, r[kOctMaxLevels];
   ChainKernel fn;
+  int tx = 0;   // whole octaves: tile width
 };
 
 #define SIFT_CHAIN_ST(M, S)                                                    \
   {M, S, 3, {5, 7, 8, 0}, k_chain<M, S, 5, 7, 8>},                             \
   {M, S, 2, {5, 7, 0, 0}, k_chain<M, S, 5, 7>}
+
+#define SIFT_OCTAVES(TX)                                                                        \
+  {kSrcUpsample, 0, 6, {5, 5, 7, 8, 10, 13}, k_octave<TX, kSrcUpsample, 0, 5, 5, 7, 8, 10, 13>, TX}, \
+  {kSrcImage, 0, 6, {7, 5, 7, 8, 10, 13}, k_octave<TX, kSrcImage, 0, 7, 5, 7, 8, 10, 13>, TX},       \
+  {kSrcDown, 0, 5, {5, 7, 8, 10, 13}, k_octave<TX, kSrcDown, 0, 5, 7, 8, 10, 13>, TX},               \
+  {kSrcDown, 1, 5, {5, 7, 8, 10, 13}, k_octave<TX, kSrcDown, 1, 5, 7, 8, 10, 13>, TX},               \
+  {kSrcDown, 2, 5, {5, 7, 8, 10, 13}, k_octave<TX, kSrcDown, 2, 5, 7, 8, 10, 13>, TX}
 
 static const ChainEntry kChains[] = {
     {kSrcUpsample, 0, 4, {5, 5, 7, 8}, k_chain<kSrcUpsample, 0, 5, 5, 7, 8>},
@@ -608,12 +792,15 @@ static const ChainEntry kChains[] = {
     SIFT_CHAIN_ST(kSrcLevel, 2),
     {kSrcLevel, 0, 2, {7, 8, 0, 0}, k_chain<kSrcLevel, 0, 7, 8>},
     {kSrcLevel, 2, 2, {7, 8, 0, 0}, k_chain<kSrcLevel, 2, 7, 8>},
+    SIFT_OCTAVES(32),
+    SIFT_OCTAVES(48),
 };
 #undef SIFT_CHAIN_ST
+#undef SIFT_OCTAVES
 
-static ChainKernel chain_kernel(int mode, int st, int n, const int* radii) {
+static ChainKernel chain_kernel(int mode, int st, int n, const int* radii, int tx) {
   for (const ChainEntry& c : kChains) {
-    if (c.mode != mode || c.st != st || c.n != n) continue;
+    if (c.mode != mode || c.st != st || c.n != n || c.tx != tx) continue;
     bool same = true;
     for (int i = 0; i < n; ++i) same = same && c.r[i] == radii[i];
     if (same) return c.fn;
@@ -622,15 +809,21 @@ static ChainKernel chain_kernel(int mode, int st, int n, const int* radii) {
 }
 
 bool chain_supported(int mode, int st, int n_levels, const int* radii) {
-  return n_levels >= 2 && n_levels <= kChainMaxLevels && chain_kernel(mode, st, n_levels, radii);
+  if (n_levels > kChainMaxLevels) {   // a whole octave: in every tile width
+    for (int tx : kOctTileW)
+      if (n_levels > kOctMaxLevels || !chain_kernel(mode, st, n_levels, radii, tx)) return false;
+    return true;
+  }
+  return n_levels >= 2 && chain_kernel(mode, st, n_levels, radii, 0);
 }
 
 hipError_t launch_chain(const ChainArgs& a, int mode, int st, int n_levels, const int* radii,
                         int grid, hipStream_t stream) {
-  if (n_levels < 2 || n_levels > kChainMaxLevels) return hipErrorInvalidValue;
-  ChainKernel fn = chain_kernel(mode, st, n_levels, radii);
-  if (!fn) return hipErrorInvalidValue;
-  return launch(fn, dim3(grid), dim3(kBlurThreads), stream, a);
+  if (n_levels < 2 || n_levels > kOctMaxLevels) return hipErrorInvalidValue;
+  const bool whole = n_levels > kChainMaxLevels;
+  ChainKernel fn = chain_kernel(mode, st, n_levels, radii, whole ? a.th : 0);
+  if (!fn || (whole && a.n > kOctMaxImages)) return hipErrorInvalidValue;
+  return launch(fn, dim3(grid), dim3(whole ? kOctThreads : kBlurThreads), stream, a);
 }
 
 // The bounds-check counter of this file's kernels (see check_in).

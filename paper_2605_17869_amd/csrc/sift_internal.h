@@ -308,6 +308,15 @@ constexpr int kChainB = 16;
 constexpr int kChainMaxLevels = 4;
 constexpr int kChainMaxR = 8;
 
+// Whole octaves (k_octave): rows and the two widths of a tile, most levels,
+// largest radius, most images of a launch (a work-group finds its image with one
+// wave scan).
+constexpr int kOctTileH = 32;
+constexpr int kOctTileW[2] = {32, 48};
+constexpr int kOctMaxLevels = 6;
+constexpr int kOctMaxR = 13;
+constexpr int kOctMaxImages = 64;
+
 struct ChainArgs {
   char* ws;
   const ImgEntry* table;
@@ -315,9 +324,9 @@ struct ChainArgs {
   int n;
   int k;            // octave slot
   int lv0;          // first level written
-  int th;           // chunk height
+  int th;           // chunk height; k_octave: tile width
   DevParams p;
-  float g[kChainMaxLevels][kChainMaxR + 1];   // g[i][t]: tap at distance t of level lv0 + i
+  float g[kOctMaxLevels][kOctMaxR + 1];   // g[i][t]: tap at distance t of level lv0 + i
 };
 
 }  // namespace sift
