@@ -139,7 +139,6 @@ sift_status sift_verify_batch(int32_t n, const sift_verify_pair* pairs, const fl
     }
     if ((e = launch_verify_setup(hd, c, stream)) != hipSuccess) return hip_fail(e, "verify setup");
   }
-  if ((e = launch_verify_prep(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify prep");
   if ((e = launch_verify_models(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify models");
   if ((e = launch_verify_hyp(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify hypotheses");
   if ((e = launch_verify_refine(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify refine");

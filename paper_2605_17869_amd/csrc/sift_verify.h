@@ -12,8 +12,9 @@
 
 namespace sift {
 
-constexpr int kVerifySetupChunk = 16;  // pair-table entries per setup launch
+constexpr int kVerifySetupChunk = 24;  // pairs per setup launch
 constexpr int kVerifyHypPerGroup = 4;  // hypotheses per work-group (one per wave)
+constexpr int kNormLargest = 6;        // where `norm` holds the largest coordinate
 constexpr int kVerifyModelBlock = 64;  // hypotheses per work-group of the model kernel (one per lane)
 
 // One pair as the kernels see it (written by the setup kernel).
@@ -31,7 +32,7 @@ struct VerifyEntry {
   int32_t pad;
   int64_t pts;       // double [cap][4]: normalised (xa, ya, xb, yb)
   int64_t raw;       // float4 [cap]: pixel (xa, ya, xb, yb), the keypoints' fp32 values
-  int64_t norm;      // double [8]: sa, txa, tya, sb, txb, tyb, n (as double), unused
+  int64_t norm;      // double [8]: sa, txa, tya, sb, txb, tyb, largest |coordinate|, unused
   int64_t scores;    // double [n_hyp]
   int64_t models;    // double [n_hyp][9]: each hypothesis' model (NaN when there is none)
 };
@@ -52,8 +53,8 @@ struct VerifySetupChunk {
   VerifyEntry e[kVerifySetupChunk];
 };
 
+// table entries and points of the chunk's pairs
 hipError_t launch_verify_setup(const VerifyHdr& h, const VerifySetupChunk& c, hipStream_t stream);
-hipError_t launch_verify_prep(const VerifyHdr& h, int n, hipStream_t stream);
 hipError_t launch_verify_models(const VerifyHdr& h, int n, hipStream_t stream);
 hipError_t launch_verify_hyp(const VerifyHdr& h, int n, hipStream_t stream);
 hipError_t launch_verify_refine(const VerifyHdr& h, int n, hipStream_t stream);

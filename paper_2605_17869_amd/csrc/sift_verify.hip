@@ -1,7 +1,7 @@
 // gfx950 kernels of geometric verification: homography hypotheses from
 // minimal samples, scored by the noise-scale-marginalised inlier likelihood,
-// the best one refined by reweighted least squares.  All arithmetic is fp64;
-// every sum runs in an order fixed by the code (per-lane partial sums in index
+// the best one refined by reweighted least squares.  All arithmetic is fp64
+// (single precision only passes over terms that are zero beyond doubt); every sum runs in an order fixed by the code (per-lane partial sums in index
 // order, then a fixed butterfly and a fixed order over waves), so results are
 // bit-identical from run to run.  Built with -ffp-contract=off.
 #include <hip/hip_runtime.h>
@@ -39,15 +39,41 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
-// Block sum of one double per thread (blockDim 256): wave butterflies, then
-// the four wave totals in wave order.  Every thread gets the same bits.
-__device__ __forceinline__ double block_sum_d(double v, double* s4) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  v = wave_sum_d(v);
-  __syncthreads();
-  if (lane == 0) s4[wave] = v;
-  __syncthreads();
-  return ((s4[0] + s4[1]) + s4[2]) + s4[3];
+// wave_sum_d of 16 values: lane l ends with the sum of value l / 4.  Every sum adds
+// the same pairs as the butterfly (lanes 32 apart, then 16, 8, 4, 2, 1), but a
+// step halves the values a lane carries on with instead of computing every sum in
+// every lane: 17 exchanges instead of 96, those over 32 and 16 lanes without LDS.
+__device__ __forceinline__ double swap_add(double a, double b, bool by32) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  uint32_t xs[2], ys[2];
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const uint32_t p = (uint32_t)(x >> (32 * w)), q = (uint32_t)(y >> (32 * w));
+    // the upper lanes of the first (odd rows of 16) change places with the lower of the second
+    const auto r = by32 ? __builtin_amdgcn_permlane32_swap(p, q, false, false)
+                        : __builtin_amdgcn_permlane16_swap(p, q, false, false);
+    xs[w] = r[0];
+    ys[w] = r[1];
+  }
+  return __builtin_bit_cast(double, ((uint64_t)xs[1] << 32) | xs[0]) +
+         __builtin_bit_cast(double, ((uint64_t)ys[1] << 32) | ys[0]);
+}
+__device__ __forceinline__ double wave_sum16_d(const double (&v)[16]) {
+  const int lane = threadIdx.x & 63;
+  double a[8], b[4], c[2];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) a[q] = swap_add(v[q], v[q + 8], true);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) b[q] = swap_add(a[q], a[q + 4], false);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const bool up = lane & 8;
+    c[q] = (up ? b[q + 2] : b[q]) + __shfl_xor(up ? b[q] : b[q + 2], 8, 64);
+  }
+  const bool up = lane & 4;
+  double d = (up ? c[1] : c[0]) + __shfl_xor(up ? c[0] : c[1], 4, 64);
+  d = d + __shfl_xor(d, 2, 64);
+  return d + __shfl_xor(d, 1, 64);
 }
 
 // Homography x -> H x of a normalised-coordinate solution h (h33 = 1) moved
@@ -78,54 +104,72 @@ __device__ __forceinline__ bool denormalise(const double* h, const double* nrm, 
   return ok;
 }
 
-// Solve the 8 x 8 system held as an augmented 8 x 9 matrix in LDS (row r at
-// A[9 r]) by Gaussian elimination with partial pivoting (first largest
-// pivot); lane r < 8 owns row r during elimination, lane 0 pivots and
-// back-substitutes.  Returns false (on every lane) when a pivot falls below
-// kPivotEps of the largest entry of the coefficient block.  Wave-level.
-__device__ bool solve8_wave(double* A, double* h) {
-  const int lane = threadIdx.x & 63;
+// The value lane i (the same for every lane) holds, in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int i) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, i);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), i);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Solve an 8 x 8 system by Gaussian elimination with partial pivoting (first
+// largest pivot): lane l holds row l % 8 of the augmented 8 x 9 matrix in A.  Rows
+// stay where they are; at[i] is the lane of the row at position i.  The pivot row
+// goes to the other lanes through scalar registers.  Returns false (on every lane)
+// when a pivot falls below kPivotEps of the largest entry of the coefficient block.
+// Wave-level.
+__device__ __forceinline__ bool solve8_wave(double (&A)[9], double* h) {
+  const int row = threadIdx.x & 7;
   double scale = 0.0;
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
+  for (int c = 0; c < 8; ++c) scale = fmax(scale, fabs(A[c]));
 #pragma unroll
-    for (int c = 0; c < 8; ++c) scale = fmax(scale, fabs(A[9 * r + c]));
+  for (int d = 4; d >= 1; d >>= 1) scale = fmax(scale, __shfl_xor(scale, d, 64));
   bool ok = scale > 0.0;
-  for (int col = 0; col < 8 && ok; ++col) {
-    // pivot row: the first of the largest |A[r][col]|, r >= col
+  int at[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) at[i] = i;
+  bool done = false;   // this lane's row has been a pivot
+#pragma unroll
+  for (int col = 0; col < 8; ++col) {
+    // pivot: the first of the largest |A[.][col]| among positions col .. 7
+    const double av = fabs(A[col]);
     int piv = col;
-    double best = fabs(A[9 * col + col]);
-    for (int r = col + 1; r < 8; ++r) {
-      const double v = fabs(A[9 * r + col]);
-      if (v > best) {
-        best = v;
-        piv = r;
+    double best = lane_value(av, at[col]);
+#pragma unroll
+    for (int i = col + 1; i < 8; ++i) {
+      const double v = lane_value(av, at[i]);
+      const bool up = v > best;
+      best = up ? v : best;
+      piv = up ? i : piv;
+    }
+    piv = __builtin_amdgcn_readfirstlane(piv);
+    ok = ok && !(best < kPivotEps * scale);
+    const int was = at[col];
+#pragma unroll
+    for (int i = col + 1; i < 8; ++i)
+      if (i == piv) {
+        at[col] = at[i];
+        at[i] = was;
       }
+    double pr[9];   // the pivot row
+#pragma unroll
+    for (int j = col; j < 9; ++j) pr[j] = lane_value(A[j], at[col]);
+    done = done || row == at[col];
+    if (!done) {
+      const double f = A[col] / pr[col];
+#pragma unroll
+      for (int j = col; j < 9; ++j) A[j] = A[j] - f * pr[j];
     }
-    if (best < kPivotEps * scale) {
-      ok = false;
-      break;
-    }
-    wave_lds_sync();
-    if (piv != col && lane < 9) {
-      const double t = A[9 * col + lane];
-      A[9 * col + lane] = A[9 * piv + lane];
-      A[9 * piv + lane] = t;
-    }
-    wave_lds_sync();
-    if (lane > col && lane < 8) {
-      const double f = A[9 * lane + col] / A[9 * col + col];
-      for (int j = col; j < 9; ++j) A[9 * lane + j] = A[9 * lane + j] - f * A[9 * col + j];
-    }
-    wave_lds_sync();
   }
-  if (!ok) return false;
-  for (int row = 7; row >= 0; --row) {
-    double acc = A[9 * row + 8];
-    for (int j = row + 1; j < 8; ++j) acc = acc - A[9 * row + j] * h[j];
-    h[row] = acc / A[9 * row + row];
+#pragma unroll
+  for (int r = 7; r >= 0; --r) {
+    double acc = lane_value(A[8], at[r]);
+#pragma unroll
+    for (int j = r + 1; j < 8; ++j) acc = acc - lane_value(A[j], at[r]) * h[j];
+    h[r] = acc / lane_value(A[r], at[r]);
   }
-  return true;
+  return ok;
 }
 
 // Rows of the DLT system of correspondence (x, y) -> (u, v), h33 = 1.
@@ -262,67 +306,150 @@ __global__ __launch_bounds__(kVerifyModelBlock) void k_verify_models(VerifyHdr h
   for (int q = 0; q < 9; ++q) out[q] = ok ? H[q] : NAN;
 }
 
-__global__ void k_verify_setup(VerifyHdr hd, VerifySetupChunk c) {
-  const int t = threadIdx.x;
-  if (t < c.count) const_cast<VerifyEntry*>(hd.table)[c.first + t] = c.e[t];
-}
+// Per pair, one work-group: its table entry (from the kernel's arguments), the
+// matched points gathered (pixels), the normalising similarity of each set (mean
+// to 0, mean distance to sqrt 2) and the normalised points.  Sums run as 256
+// partial sums, partial sum v over correspondences v, v + 256, ..., whatever the
+// number of threads that gather.  Bound: the latency of its dependent loads: 7 us for
+// one pair of 211 matches, 11 for up to kVerifySetupChunk pairs of 1300; the table in
+// a launch of its own and a preparation by 256 threads took 10 and 16.
+constexpr int kPrepThreads = 1024, kPrepHeld = 4096;   // threads; points kept in LDS
 
-// Per pair: gather the matched points (pixels), the normalising similarity of
-// each set (mean to 0, mean distance to sqrt 2) and the normalised points.
-__global__ __launch_bounds__(256) void k_verify_prep(VerifyHdr hd, int n_pairs) {
+__global__ __launch_bounds__(kPrepThreads) void k_verify_prep(VerifyHdr hd, VerifySetupChunk c) {
   __shared__ double s4[4];
-  const VerifyEntry e = hd.table[blockIdx.x];
+  __shared__ float4 s_raw[kPrepHeld];
+  __shared__ float s_max[kPrepThreads / 64];
+  const VerifyEntry e = c.e[blockIdx.x];
+  const int t = threadIdx.x;
+  if (t == 0) const_cast<VerifyEntry*>(hd.table)[c.first + blockIdx.x] = e;
   const int n = verify_count(e);
   float4* raw = reinterpret_cast<float4*>(hd.ws + e.raw);
   double* pts = reinterpret_cast<double*>(hd.ws + e.pts);
   double* nrm = reinterpret_cast<double*>(hd.ws + e.norm);
-  double sx[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int i = threadIdx.x; i < n; i += 256) {
+  float largest = 0.0f;
+  for (int i = t; i < n; i += kPrepThreads) {
     SIFT_CHECK_INDEX(i, e.cap);
     const sift_match m = e.matches[i];
     const sift_keypoint ka = e.kp_a[m.query], kb = e.kp_b[m.train];
-    raw[i] = make_float4(ka.x, ka.y, kb.x, kb.y);
-    const double v[4] = {(double)ka.x, (double)ka.y, (double)kb.x, (double)kb.y};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sx[q] += v[q];
+    const float4 v = make_float4(ka.x, ka.y, kb.x, kb.y);
+    raw[i] = v;
+    if (i < kPrepHeld) s_raw[i] = v;
+    largest = fmaxf(largest, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
   }
-  double c[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) c[q] = block_sum_d(sx[q], s4) / (double)(n > 0 ? n : 1);
+  largest = wave_max(largest);
+  if ((t & 63) == 0) s_max[t >> 6] = largest;
   __syncthreads();
-  double da = 0.0, db = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    SIFT_CHECK_INDEX(i, e.cap);
-    const RawPt q = raw_at(raw, i);
-    const double xa = q.ax - c[0], ya = q.ay - c[1], xb = q.bx - c[2], yb = q.by - c[3];
-    da += sqrt(xa * xa + ya * ya);
-    db += sqrt(xb * xb + yb * yb);
+  auto point = [&](int i) {
+    if (i < kPrepHeld) return raw_at(s_raw, i);
+    return raw_at(raw, i);
+  };
+  // sums of the first four waves' partial sums, in wave order
+  auto sum = [&](double v) {
+    v = wave_sum_d(v);
+    __syncthreads();
+    if (t < 256 && (t & 63) == 0) s4[t >> 6] = v;
+    __syncthreads();
+    return ((s4[0] + s4[1]) + s4[2]) + s4[3];
+  };
+  double sx[4] = {0.0, 0.0, 0.0, 0.0};
+  if (t < 256) {
+    for (int i = t; i < n; i += 256) {
+      SIFT_CHECK_INDEX(i, e.cap);
+      const RawPt q = point(i);
+      sx[0] += q.ax;
+      sx[1] += q.ay;
+      sx[2] += q.bx;
+      sx[3] += q.by;
+    }
   }
-  const double ma = block_sum_d(da, s4) / (double)(n > 0 ? n : 1);
-  const double mb = block_sum_d(db, s4) / (double)(n > 0 ? n : 1);
+  double m[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) m[q] = sum(sx[q]) / (double)(n > 0 ? n : 1);
+  double da = 0.0, db = 0.0;
+  if (t < 256) {
+    for (int i = t; i < n; i += 256) {
+      SIFT_CHECK_INDEX(i, e.cap);
+      const RawPt q = point(i);
+      const double xa = q.ax - m[0], ya = q.ay - m[1], xb = q.bx - m[2], yb = q.by - m[3];
+      da += sqrt(xa * xa + ya * ya);
+      db += sqrt(xb * xb + yb * yb);
+    }
+  }
+  const double ma = sum(da) / (double)(n > 0 ? n : 1);
+  const double mb = sum(db) / (double)(n > 0 ? n : 1);
   const double sa = ma > 0.0 ? kSqrt2 / ma : 1.0, sb = mb > 0.0 ? kSqrt2 / mb : 1.0;
-  const double t[6] = {sa, -sa * c[0], -sa * c[1], sb, -sb * c[2], -sb * c[3]};
-  if (threadIdx.x < 6) nrm[threadIdx.x] = t[threadIdx.x];
-  for (int i = threadIdx.x; i < n; i += 256) {
+  const double T[6] = {sa, -sa * m[0], -sa * m[1], sb, -sb * m[2], -sb * m[3]};
+  if (t < 6) nrm[t] = T[t];
+  if (t == 6) {
+    for (int w = 1; w < kPrepThreads / 64; ++w) largest = fmaxf(largest, s_max[w]);
+    nrm[kNormLargest] = (double)fmaxf(largest, s_max[0]);
+  }
+  for (int i = t; i < n; i += kPrepThreads) {
     SIFT_CHECK_INDEX(i, e.cap);
-    const RawPt q = raw_at(raw, i);
+    const RawPt q = point(i);
     double* o = pts + 4 * (int64_t)i;
-    o[0] = sa * q.ax + t[1];
-    o[1] = sa * q.ay + t[2];
-    o[2] = sb * q.bx + t[4];
-    o[3] = sb * q.by + t[5];
+    o[0] = sa * q.ax + T[1];
+    o[1] = sa * q.ay + T[2];
+    o[2] = sb * q.bx + T[4];
+    o[3] = sb * q.by + T[5];
   }
 }
 
+// A test in single precision that every correspondence passes that weight_at's
+// does (and few others).  With u = 2^-24, C the largest coordinate and X, Y, W the
+// largest |x|, |y|, |w| that coordinates up to C can give under H, the computed x, y, w
+// (entries of H rounded, two fused steps) are within 4 u X, 4 u Y, 4 u W, and
+// ex = x - bx w within 5.1 u (X + C W).  Its test means |(ex, ey)| < L w with
+// L = tau smax (1 + 5e-10), so the computed values satisfy |(ex, ey)| < L w + K,
+// K = 4 u L W + 5.1 u (X + Y + 2 C W); K is taken with 8 u (and a floor far above the
+// smallest numbers), the comparison of squares with 1e-6 to spare.  The conditions are
+// written so that NaN and infinity pass.
+struct Admit32 {
+  float h[9], L, K;
+  __device__ __forceinline__ Admit32(const double* H, double smax, float C) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) h[q] = (float)H[q];
+    L = (float)(kTau * smax) * 1.000001f;
+    const float X = C * (fabsf(h[0]) + fabsf(h[1])) + fabsf(h[2]);
+    const float Y = C * (fabsf(h[3]) + fabsf(h[4])) + fabsf(h[5]);
+    const float W = C * (fabsf(h[6]) + fabsf(h[7])) + fabsf(h[8]);
+    K = 4.76837158e-7f * (L * W + ((X + Y) + 2.0f * (C * W))) + 1e-25f;
+  }
+  __device__ __forceinline__ bool operator()(const float4& p) const {
+    const float x = __fmaf_rn(p.x, h[0], __fmaf_rn(p.y, h[1], h[2]));
+    const float y = __fmaf_rn(p.x, h[3], __fmaf_rn(p.y, h[4], h[5]));
+    const float w = __fmaf_rn(p.x, h[6], __fmaf_rn(p.y, h[7], h[8]));
+    const float ex = __fmaf_rn(-p.z, w, x), ey = __fmaf_rn(-p.w, w, y);
+    const float t = __fmaf_rn(L, w, K);
+    const float d2 = __fmaf_rn(ex, ex, ey * ey), t2 = (t * t) * 1.000001f;
+    return !(t <= 0.0f) & !(d2 > t2);
+  }
+};
+
 // One wave per hypothesis: its score, the sum over the pair's correspondences
-// of the marginal likelihood of the residual under its stored model.
+// of the marginal likelihood of the residual under its stored model (lane l adds
+// the weights of l, l + 64, ... in that order, then a fixed butterfly).
+//
+// Most correspondences are far from most hypotheses.  A wave tests kHypChunk of
+// them in single precision (Admit32), packs those that pass, computes their weights
+// in double precision with every lane busy (the exact test among it), and each lane
+// then adds its own.  Testing all in double precision and entering the weight (three
+// divisions, root, error function) wherever any of 64 lanes needs it took 187 us
+// for 32 pairs of 1300 matches and 1500 hypotheses, this takes 135; packing alone
+// did not help, the test was the cost.  Bound: VALU work (1100 instructions a wave,
+// 87 us of issue).
+constexpr int kHypChunk = 1024;
+
 __global__ __launch_bounds__(64 * kVerifyHypPerGroup) void k_verify_hyp(VerifyHdr hd, int n_pairs) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ double s_w[kVerifyHypPerGroup][kHypChunk];
+  __shared__ uint16_t s_at[kVerifyHypPerGroup][kHypChunk];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int p = blockIdx.x / hd.hyp_groups;
   const int k = (blockIdx.x - p * hd.hyp_groups) * kVerifyHypPerGroup + wave;
   if (k >= hd.n_hyp) return;
   const VerifyEntry e = hd.table[p];
-  const int n = verify_count(e);
+  const int n = __builtin_amdgcn_readfirstlane(verify_count(e));
   double* scores = reinterpret_cast<double*>(hd.ws + e.scores);
   SIFT_CHECK_INDEX(k, hd.n_hyp);
   const double* model = reinterpret_cast<const double*>(hd.ws + e.models) + 9 * (int64_t)k;
@@ -333,12 +460,52 @@ __global__ __launch_bounds__(64 * kVerifyHypPerGroup) void k_verify_hyp(VerifyHd
     if (lane == 0) scores[k] = -INFINITY;
     return;
   }
+  const Admit32 near(H, hd.sigma_max,
+                     (float)reinterpret_cast<const double*>(hd.ws + e.norm)[kNormLargest]);
   const float4* raw = reinterpret_cast<const float4*>(hd.ws + e.raw);
+  double* const w_of = s_w[wave];
+  uint16_t* const at = s_at[wave];
   double acc = 0.0;
-  for (int i = lane; i < n; i += 64) {
-    SIFT_CHECK_INDEX(i, e.cap);
-    const RawPt q = raw_at(raw, i);
-    acc += weight_at(H, q.ax, q.ay, q.bx, q.by, hd.sigma_max);
+  for (int base = 0; base < n; base += kHypChunk) {
+    const int m = min(n - base, kHypChunk);
+    uint32_t mine = 0;   // bit j: correspondence base + 64 j + lane is near
+    int count = 0;       // near ones so far (the same for every lane)
+    constexpr int U = 4; // rows of 64 whose points are loaded together
+    for (int j0 = 0; 64 * j0 < m; j0 += U) {
+      float4 q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = min(64 * (j0 + u) + lane, m - 1);
+        SIFT_CHECK_INDEX(base + i, e.cap);
+        q[u] = raw[base + i];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = 64 * (j0 + u) + lane;
+        const bool in = (i < m) & near(q[u]);
+        const uint64_t b = __ballot(in);
+        if (in) {
+          mine |= 1u << (j0 + u);
+          at[count + __popcll(b & lanemask_lt())] = (uint16_t)i;
+        }
+        count += __popcll(b);
+      }
+    }
+    wave_lds_sync();
+    for (int c = lane; c < count; c += 64) {
+      const int i = at[c];
+      SIFT_CHECK_INDEX(i, m);
+      const RawPt q = raw_at(raw, base + i);
+      w_of[i] = weight_at(H, q.ax, q.ay, q.bx, q.by, hd.sigma_max);
+    }
+    wave_lds_sync();
+    // the others add +0 to a sum that is not negative: left out
+    while (mine) {
+      const int j = __builtin_ctz(mine);
+      mine &= mine - 1u;
+      acc += w_of[64 * j + lane];
+    }
+    wave_lds_sync();
   }
   acc = wave_sum_d(acc);
   if (lane == 0) scores[k] = acc;
@@ -347,15 +514,47 @@ __global__ __launch_bounds__(64 * kVerifyHypPerGroup) void k_verify_hyp(VerifyHd
 // Per pair: the best hypothesis (largest score, first among equals), then
 // reweighted least squares on the normalised DLT rows, each step kept only
 // if it raises the score; outputs the model, score, inlier count, weights.
-__global__ __launch_bounds__(256) void k_verify_refine(VerifyHdr hd, int n_pairs) {
+//
+// Sums run as 256 partial sums, partial sum v over correspondences v, v + 256,
+// ..., then the butterfly of each 64, then the four in order.  The weights under a
+// model are computed once, by all threads, and kept in LDS for the score,
+// the next step's normal equations and the output; the 35 entries of the normal
+// equations that are not zero by construction or equal to another are split over
+// the two groups of 256 threads.  Bound: latency (one work-group per pair; at 211
+// matches 6.9 us a step, of which 3.8 are the 8 x 8 system's chain of divisions).
+// With 256 threads for everything, all 44 entries per thread and lane, weights
+// computed for every use and the systems solved in LDS a pair of 211 matches took
+// 48 us and 32 pairs of 1300 took 109 us; this takes 27 and 59.  1024 threads spilled
+// registers (66 us); a full butterfly for each of 16 sums cost 4.5 us a step.
+constexpr int kRefineThreads = 512;
+constexpr int kRefineHeld = 4096;   // weights kept in LDS; longer sets go by chunks of as many
+constexpr int kRefineSums = 16;     // sums per thread
+
+// Where entry q of the normal equations' upper triangle (rows of 8, 7, .. 1
+// entries, then the right side) is summed: group * kRefineSums + sum, -1: zero.
+// Rows 3, 4, 5 (x, y, 1 of the second DLT row) repeat rows 0, 1, 2 among themselves.
+__device__ const signed char kNormalAt[44] = {
+    0, 1, 2, -1, -1, -1, 16, 17,   // (0, 0..7)
+    3, 4, -1, -1, -1, 18, 19,      // (1, 1..7)
+    5, -1, -1, -1, 20, 21,         // (2, 2..7)
+    0, 1, 2, 24, 25,               // (3, 3..7)
+    3, 4, 26, 27,                  // (4, 4..7)
+    5, 28, 29,                     // (5, 5..7)
+    6, 7,                          // (6, 6..7)
+    22,                            // (7, 7)
+    8, 9, 10, 11, 12, 13, 14, 15}; // right side
+
+__global__ __launch_bounds__(kRefineThreads) void k_verify_refine(VerifyHdr hd, int n_pairs) {
+  __shared__ double s_w[2][kRefineHeld];
   __shared__ double s4[4];
-  __shared__ double s_a[72];
-  __shared__ double s_ne[4][44];
+  __shared__ double s_red[4][2 * kRefineSums];   // [wave of a group][group, sum]
   __shared__ double s_h[9];
-  __shared__ int s_flag;
-  __shared__ double s_bv[4];
-  __shared__ int s_bi[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ int s_flag, s_cnt;
+  __shared__ double s_bv[kRefineThreads / 64];
+  __shared__ int s_bi[kRefineThreads / 64];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int group = wave >> 2, v0 = t & 255;   // group of 256 threads; partial sum
   const VerifyEntry e = hd.table[blockIdx.x];
   const int n = verify_count(e);
   const double* scores = reinterpret_cast<const double*>(hd.ws + e.scores);
@@ -367,7 +566,7 @@ __global__ __launch_bounds__(256) void k_verify_refine(VerifyHdr hd, int n_pairs
   double bv = -INFINITY;
   int bi = 0x7fffffff;
   if (n >= 4) {
-    for (int k = threadIdx.x; k < hd.n_hyp; k += 256) {
+    for (int k = t; k < hd.n_hyp; k += kRefineThreads) {
       const double v = scores[k];
       if (v > bv || (v == bv && k < bi)) {
         bv = v;
@@ -388,24 +587,25 @@ __global__ __launch_bounds__(256) void k_verify_refine(VerifyHdr hd, int n_pairs
     s_bv[wave] = bv;
     s_bi[wave] = bi;
   }
+  if (t == 0) s_cnt = 0;
   __syncthreads();
   bv = s_bv[0];
   bi = s_bi[0];
-  for (int w = 1; w < 4; ++w)
+  for (int w = 1; w < kRefineThreads / 64; ++w)
     if (s_bv[w] > bv || (s_bv[w] == bv && s_bi[w] < bi)) {
       bv = s_bv[w];
       bi = s_bi[w];
     }
   if (!(bv > -INFINITY)) {
     // no hypothesis: NaN model, zero score and inliers
-    if (threadIdx.x < 9) e.H[threadIdx.x] = NAN;
-    if (threadIdx.x == 0) {
+    if (t < 9) e.H[t] = NAN;
+    if (t == 0) {
       *e.score = 0.0;
       *e.n_inliers = 0;
       if (e.best) *e.best = -1;
     }
     if (e.weights)
-      for (int i = threadIdx.x; i < e.cap; i += 256) e.weights[i] = 0.0f;
+      for (int i = t; i < e.cap; i += kRefineThreads) e.weights[i] = 0.0f;
     return;
   }
   // the best hypothesis' model, as stored
@@ -416,62 +616,93 @@ __global__ __launch_bounds__(256) void k_verify_refine(VerifyHdr hd, int n_pairs
 #pragma unroll
     for (int q = 0; q < 9; ++q) H[q] = model[q];
   }
-  double Q = bv;
-  for (int it = 0; it < hd.refine_iters; ++it) {
-    // weighted normal equations of the DLT rows (upper triangle + rhs)
-    double ne[44];
-#pragma unroll
-    for (int q = 0; q < 44; ++q) ne[q] = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
+  // weights of correspondences base .. base + kRefineHeld - 1 under G
+  auto weigh = [&](const double* G, int base, double* buf) {
+    for (int i = base + t; i < min(n, base + kRefineHeld); i += kRefineThreads) {
       SIFT_CHECK_INDEX(i, e.cap);
       const RawPt r = raw_at(raw, i);
-      const double w = weight_at(H, r.ax, r.ay, r.bx, r.by, hd.sigma_max);
-      const double* p = pts + 4 * (int64_t)i;
-      double r1[9], r2[9];
-      dlt_rows(p[0], p[1], p[2], p[3], r1, r2);
-      int q = 0;
-#pragma unroll
-      for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = a; b < 8; ++b) {
-          ne[q] = ne[q] + r1[a] * (w * r1[b]);
-          ne[q] = ne[q] + r2[a] * (w * r2[b]);
-          ++q;
+      buf[i - base] = weight_at(G, r.ax, r.ay, r.bx, r.by, hd.sigma_max);
+    }
+  };
+  const bool held = n <= kRefineHeld;
+  int cur = 0;   // held: the buffer with the weights under H
+  if (held) weigh(H, 0, s_w[0]);
+  double Q = bv;
+  for (int it = 0; it < hd.refine_iters; ++it) {
+    // weighted normal equations of the DLT rows (x, y, 1, 0, 0, 0, -u x, -u y; u)
+    // and (0, 0, 0, x, y, 1, -v x, -v y; v): this group's sums of a (w b)
+    double ne[kRefineSums] = {};
+    for (int base = 0; base < n; base += kRefineHeld) {
+      if (!held) {
+        __syncthreads();
+        weigh(H, base, s_w[0]);
+      }
+      __syncthreads();
+      const double* w_of = s_w[held ? cur : 0];
+      for (int i = base + v0; i < min(n, base + kRefineHeld); i += 256) {
+        SIFT_CHECK_INDEX(i, e.cap);
+        const double w = w_of[i - base];
+        const double* p = pts + 4 * (int64_t)i;
+        const double x = p[0], y = p[1], u = p[2], v = p[3];
+        const double ux = -u * x, uy = -u * y, vx = -v * x, vy = -v * y;
+        if (group == 0) {
+          const double wx = w * x, wy = w * y, wu = w * u, wv = w * v;
+          ne[0] = ne[0] + x * wx;
+          ne[1] = ne[1] + x * wy;
+          ne[2] = ne[2] + x * w;
+          ne[3] = ne[3] + y * wy;
+          ne[4] = ne[4] + y * w;
+          ne[5] = ne[5] + w;
+          ne[6] = ne[6] + ux * (w * ux);
+          ne[6] = ne[6] + vx * (w * vx);
+          ne[7] = ne[7] + ux * (w * uy);
+          ne[7] = ne[7] + vx * (w * vy);
+          ne[8] = ne[8] + x * wu;
+          ne[9] = ne[9] + y * wu;
+          ne[10] = ne[10] + wu;
+          ne[11] = ne[11] + x * wv;
+          ne[12] = ne[12] + y * wv;
+          ne[13] = ne[13] + wv;
+          ne[14] = ne[14] + ux * wu;
+          ne[14] = ne[14] + vx * wv;
+          ne[15] = ne[15] + uy * wu;
+          ne[15] = ne[15] + vy * wv;
+        } else {
+          const double wux = w * ux, wuy = w * uy, wvx = w * vx, wvy = w * vy;
+          ne[0] = ne[0] + x * wux;
+          ne[1] = ne[1] + x * wuy;
+          ne[2] = ne[2] + y * wux;
+          ne[3] = ne[3] + y * wuy;
+          ne[4] = ne[4] + wux;
+          ne[5] = ne[5] + wuy;
+          ne[6] = ne[6] + uy * wuy;
+          ne[6] = ne[6] + vy * wvy;
+          ne[8] = ne[8] + x * wvx;
+          ne[9] = ne[9] + x * wvy;
+          ne[10] = ne[10] + y * wvx;
+          ne[11] = ne[11] + y * wvy;
+          ne[12] = ne[12] + wvx;
+          ne[13] = ne[13] + wvy;
         }
-#pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        ne[q] = ne[q] + r1[a] * (w * r1[8]);
-        ne[q] = ne[q] + r2[a] * (w * r2[8]);
-        ++q;
       }
     }
-#pragma unroll
-    for (int q = 0; q < 44; ++q) ne[q] = wave_sum_d(ne[q]);
-    __syncthreads();
-    if (lane == 0)
-#pragma unroll
-      for (int q = 0; q < 44; ++q) s_ne[wave][q] = ne[q];
+    const double sum = wave_sum16_d(ne);
+    if ((lane & 3) == 0) s_red[wave & 3][group * kRefineSums + (lane >> 2)] = sum;
     __syncthreads();
     if (wave == 0) {
-      // the system in LDS (lanes 0..43 each sum one entry over the waves)
-      if (lane < 44) {
-        const double v = ((s_ne[0][lane] + s_ne[1][lane]) + s_ne[2][lane]) + s_ne[3][lane];
-        if (lane < 36) {
-          int a = 0, rem = lane;
-          while (rem >= 8 - a) {
-            rem -= 8 - a;
-            ++a;
-          }
-          const int b = a + rem;
-          s_a[9 * a + b] = v;
-          s_a[9 * b + a] = v;
-        } else {
-          s_a[9 * (lane - 36) + 8] = v;
-        }
+      // lane l: row l % 8 of the system
+      double A[9];
+      const int r = lane & 7;
+#pragma unroll
+      for (int j = 0; j < 9; ++j) {
+        const int a = min(r, j), b = max(r, j);
+        const int at = kNormalAt[j == 8 ? 36 + r : 8 * a - a * (a - 1) / 2 + (b - a)];
+        const int i = max(at, 0);
+        const double v = ((s_red[0][i] + s_red[1][i]) + s_red[2][i]) + s_red[3][i];
+        A[j] = at < 0 ? 0.0 : v;
       }
-      wave_lds_sync();
       double h[8], H2[9];
-      bool ok = solve8_wave(s_a, h);
+      bool ok = solve8_wave(A, h);
       if (ok) ok = denormalise(h, nrm, H2);
       if (lane == 0) {
         s_flag = ok ? 1 : 0;
@@ -484,44 +715,52 @@ __global__ __launch_bounds__(256) void k_verify_refine(VerifyHdr hd, int n_pairs
 #pragma unroll
     for (int q = 0; q < 9; ++q) H2[q] = s_h[q];
     double acc = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
-      SIFT_CHECK_INDEX(i, e.cap);
-      const RawPt r = raw_at(raw, i);
-      acc += weight_at(H2, r.ax, r.ay, r.bx, r.by, hd.sigma_max);
+    double* const w_new = s_w[held ? cur ^ 1 : 0];
+    for (int base = 0; base < n; base += kRefineHeld) {
+      if (base > 0) __syncthreads();   // the chunk before has been added
+      weigh(H2, base, w_new);
+      __syncthreads();
+      if (group == 0)
+        for (int i = base + v0; i < min(n, base + kRefineHeld); i += 256) acc += w_new[i - base];
     }
-    const double Q2 = block_sum_d(acc, s4);
+    acc = wave_sum_d(acc);
+    if (group == 0 && lane == 0) s4[wave] = acc;
+    __syncthreads();
+    const double Q2 = ((s4[0] + s4[1]) + s4[2]) + s4[3];
     if (!(Q2 > Q)) break;
 #pragma unroll
     for (int q = 0; q < 9; ++q) H[q] = H2[q];
     Q = Q2;
+    cur ^= 1;
   }
   // outputs
-  double cnt = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    SIFT_CHECK_INDEX(i, e.cap);
-    const RawPt r = raw_at(raw, i);
-    const double w = weight_at(H, r.ax, r.ay, r.bx, r.by, hd.sigma_max);
-    cnt += w > 0.0 ? 1.0 : 0.0;
-    SIFT_CHECK_INDEX(i, e.cap);
-    if (e.weights) e.weights[i] = (float)w;
+  __syncthreads();
+  int cnt = 0;
+  for (int base = 0; base < n; base += kRefineHeld) {
+    if (!held) weigh(H, base, s_w[0]);   // every thread reads back its own
+    for (int i = base + t; i < min(n, base + kRefineHeld); i += kRefineThreads) {
+      SIFT_CHECK_INDEX(i, e.cap);
+      const double w = s_w[held ? cur : 0][i - base];
+      cnt += w > 0.0 ? 1 : 0;
+      if (e.weights) e.weights[i] = (float)w;
+    }
   }
   if (e.weights)
-    for (int i = n + threadIdx.x; i < e.cap; i += 256) e.weights[i] = 0.0f;
-  const double inl = block_sum_d(cnt, s4);
-  if (threadIdx.x < 9) e.H[threadIdx.x] = H[threadIdx.x];
-  if (threadIdx.x == 0) {
+    for (int i = n + t; i < e.cap; i += kRefineThreads) e.weights[i] = 0.0f;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
+  if (lane == 0) atomicAdd(&s_cnt, cnt);
+  __syncthreads();
+  if (t < 9) e.H[t] = H[t];
+  if (t == 0) {
     *e.score = Q;
-    *e.n_inliers = (int)inl;
+    *e.n_inliers = s_cnt;
     if (e.best) *e.best = bi;
   }
 }
 
 hipError_t launch_verify_setup(const VerifyHdr& h, const VerifySetupChunk& c, hipStream_t stream) {
-  return launch(k_verify_setup, dim3(1), dim3(64), stream, h, c);
-}
-
-hipError_t launch_verify_prep(const VerifyHdr& h, int n, hipStream_t stream) {
-  return launch(k_verify_prep, dim3(n), dim3(256), stream, h, n);
+  return launch(k_verify_prep, dim3(c.count), dim3(kPrepThreads), stream, h, c);
 }
 
 hipError_t launch_verify_models(const VerifyHdr& h, int n, hipStream_t stream) {
@@ -534,7 +773,7 @@ hipError_t launch_verify_hyp(const VerifyHdr& h, int n, hipStream_t stream) {
 }
 
 hipError_t launch_verify_refine(const VerifyHdr& h, int n, hipStream_t stream) {
-  return launch(k_verify_refine, dim3(n), dim3(256), stream, h, n);
+  return launch(k_verify_refine, dim3(n), dim3(kRefineThreads), stream, h, n);
 }
 
 // The bounds-check counter of this file's kernels (see check_index).
