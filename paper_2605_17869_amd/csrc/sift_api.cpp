@@ -522,12 +522,19 @@ HdrPtrs header_ptrs(char* ws, int n) {
 
 // The image table: entries[i] copied into the workspace, a chunk of entries
 // per setup launch (kernel arguments carry them; nothing is copied from host
-// memory by the runtime).
+// memory by the runtime).  Where one launch takes them all it makes the prefix
+// tables, too.
+bool finalized_by_table(int n) { return n <= kSetupChunk; }
+
 sift_status write_table(const std::vector<ImgEntry>& entries, const HdrPtrs& hp,
-                        hipStream_t stream) {
+                        const DevParams& p, hipStream_t stream) {
   SetupChunk chunk;
   std::memset(&chunk, 0, sizeof chunk);
   const int n = (int)entries.size();
+  if (finalized_by_table(n)) {
+    chunk.n = n;
+    chunk.p = p;
+  }
   for (int i = 0; i < n; ++i) {
     chunk.e[chunk.count] = entries[i];
     if (++chunk.count == kSetupChunk || i == n - 1) {
@@ -558,19 +565,20 @@ ImgEntry make_entry(const float* img, int64_t pitch, int height, int width, int6
   return e;
 }
 
-// Every stage after the table is in place: prefix tables, pyramid, detection,
+// Every stage after the table is in place: prefix tables (unless finalized), pyramid, detection,
 // compaction, refinement, orientation, descriptors.  Grids come from `plan`;
 // each kernel reads the actual work counts from the table on the device and
 // lets surplus work-groups go, so a plan may over-cover the images.
 sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, const Plan& plan,
-                          char* ws, const HdrPtrs& hp, hipStream_t stream) {
+                          char* ws, const HdrPtrs& hp, bool finalized, hipStream_t stream) {
   sift_status st = SIFT_OK;
   const DevParams& p = cfg.dev;
   for (int64_t t : plan.tiles)
     if (t > INT32_MAX - kXcds) return fail(SIFT_ERR_TOO_LARGE, "batch has too many tiles");
   if (plan.bands > INT32_MAX - kXcds) return fail(SIFT_ERR_TOO_LARGE, "batch has too many bands");
   int prec = prof_begin(kStSetup, 0.0, stream);
-  if ((st = check_hip(launch_finalize(hp, n, p, stream), "finalize")) != SIFT_OK) return st;
+  if (!finalized && (st = check_hip(launch_finalize(hp, n, p, stream), "finalize")) != SIFT_OK)
+    return st;
   prof_end(prec, stream);
 
   // scale space: per octave, runs of consecutive levels in one launch each
@@ -694,9 +702,7 @@ sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, co
   prof_end(prec, stream);
   prec = prof_begin(kStCompact, (p.s / 4.0) * all_px, stream);
   if ((st = check_hip(launch_band_scan(ws, hp, n, p, stream), "band scan")) != SIFT_OK) return st;
-  if (bands > 0 && (st = check_hip(launch_emit(ws, hp, n, p, bands, stream), "emit")) != SIFT_OK)
-    return st;
-  if ((st = check_hip(launch_img_prefix(ws, hp, n, p, 0, stream), "prefix")) != SIFT_OK) return st;
+  if ((st = check_hip(launch_emit(ws, hp, n, p, bands, stream), "emit")) != SIFT_OK) return st;
   prof_end(prec, stream);
   // per-candidate stages; grids are persistent, work counts are read on the device
   const int64_t cand_total = (int64_t)n * p.max_cand;
@@ -708,7 +714,6 @@ sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, co
   prec = prof_begin(kStOrient, 0.0, stream);
   if ((st = check_hip(launch_orient(ws, hp, n, p, orient_grid, stream), "orient")) != SIFT_OK) return st;
   if ((st = check_hip(launch_ori_scan(ws, hp, n, p, stream), "orientation scan")) != SIFT_OK) return st;
-  if ((st = check_hip(launch_img_prefix(ws, hp, n, p, 1, stream), "prefix")) != SIFT_OK) return st;
   prof_end(prec, stream);
   const int desc_grid = (int)std::min<int64_t>(1024, std::max<int64_t>(1, cand_total));
   prec = prof_begin(kStDescribe, 0.0, stream);
@@ -737,10 +742,10 @@ sift_status launch_batch(const sift_handle* h, const Config& cfg, int32_t n,
     plan_add(&plan, p, heights[i], widths[i], 1);
   }
   const int prec = prof_begin(kStSetup, 0.0, stream);
-  sift_status st = write_table(entries, hp, stream);
+  sift_status st = write_table(entries, hp, p, stream);
   prof_end(prec, stream);
   if (st != SIFT_OK) return st;
-  return launch_stages(h, cfg, n, plan, ws, hp, stream);
+  return launch_stages(h, cfg, n, plan, ws, hp, finalized_by_table(n), stream);
 }
 
 }  // namespace
@@ -858,6 +863,7 @@ struct sift_bucket {
   int64_t slot_bytes = 0;   // one image region at the largest size
   int64_t sink = 0;         // scratch outputs of empty slots
   int64_t slots = 0;        // first slot region
+  DevParams dev;            // for the table's launch, which may finalize
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -924,7 +930,7 @@ sift_status sift_bucket_create(sift_handle* h, int32_t n_slots, int32_t max_heig
     return check_hip(e, "begin capture");
   }
   sift::set_capturing(true);
-  st = launch_stages(h, c, n_slots, plan, ws, hp, cap);
+  st = launch_stages(h, c, n_slots, plan, ws, hp, finalized_by_table(n_slots), cap);
   sift::set_capturing(false);
   hipGraph_t graph = nullptr;
   e = hipStreamEndCapture(cap, &graph);
@@ -950,6 +956,7 @@ sift_status sift_bucket_create(sift_handle* h, int32_t n_slots, int32_t max_heig
   b->slot_bytes = sb;
   b->sink = sink;
   b->slots = slots;
+  b->dev = c.dev;
   b->graph = graph;
   b->exec = exec;
   *out = b;
@@ -995,7 +1002,7 @@ sift_status sift_bucket_launch(sift_bucket* b, int32_t n, const float* const* d_
       entries.push_back(make_entry(reinterpret_cast<const float*>(b->ws + b->sink), 0, 0, 0,
                                    region, sink));
   }
-  sift_status st = write_table(entries, header_ptrs(b->ws, b->n_slots), stream);
+  sift_status st = write_table(entries, header_ptrs(b->ws, b->n_slots), b->dev, stream);
   if (st != SIFT_OK) return st;
   return check_hip(hipGraphLaunch(b->exec, stream), "bucket launch");
 }

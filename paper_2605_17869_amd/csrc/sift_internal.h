@@ -216,7 +216,7 @@ struct Header {
   int64_t band_prefix;     // int32 [n + 1]
   int64_t cand_prefix;     // int32 [n + 1]: refined candidates per image
   int64_t kp_prefix;       // int32 [n + 1]: described keypoints per image
-  int64_t queue;           // int32 [kQueues]: work counter 0 of the descriptor, the rest unused
+  int64_t queue;           // int32 [kQueues]: work counter 0, images counted, the rest unused
   int64_t bytes;
 };
 

@@ -17,61 +17,63 @@
 namespace sift {
 
 // ---------------------------------------------------------------------------
-// Setup: copy image-table entries from kernel arguments into the workspace,
-// then derive the per-octave tile and per-image band prefix sums.
+// Setup: image-table entries copied from kernel arguments into the workspace, and
+// prefix sums over the batch of the blur work items of every (chunk class, octave)
+// and of the detection bands.  A wave takes every kSetupWaves-th table, 64 images at
+// a time, one lane each.  Where the arguments hold every image one launch does both
+// (4.9 us for one image; as two launches, the tables by one wave, 15.6).
+constexpr int kSetupWaves = 16;
 
-__global__ void k_setup(HdrPtrs hp, SetupChunk c) {
-  const int t = threadIdx.x;
-  if (t < c.count) const_cast<ImgEntry*>(hp.table)[c.first + t] = c.e[t];
-}
-
-// Prefix sums over the batch of the blur work items of every (chunk class,
-// octave) and of the detection bands, one wave, 64 images at a time: lane i
-// takes image i0 + i, each table is one wave scan, and lane t keeps the
-// running total of table t between chunks.
-static_assert(kNumTileH * kMaxOct + 1 <= 64, "one lane per table");
+// Images whose keypoints are counted (k_ori_scan).
+__device__ __forceinline__ int* images_done(const HdrPtrs& hp) { return hp.queue + 1; }
 
 // Work counter i of the launch sequence (i < min(n, kQueues)).
-__device__ __forceinline__ int* work_counter(const HdrPtrs& hp, int i) {
-  return i == 0 ? hp.queue : &counters_of(hp.ws, hp.table[i])[kCntQueue];
+__device__ __forceinline__ int* work_counter(const HdrPtrs& hp, const ImgEntry* tab, int i) {
+  return i == 0 ? hp.queue : &counters_of(hp.ws, tab[i])[kCntQueue];
 }
 
-__global__ void k_finalize(HdrPtrs hp, int n, DevParams p) {
-  const ImgEntry* tab = hp.table;
+__device__ __forceinline__ void prefix_tables(const HdrPtrs& hp, const ImgEntry* tab, int n,
+                                              const DevParams& p) {
   const LayoutCfg lc = layout_cfg(p);
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   const int ntile = kNumTileH * p.n_oct;   // tables 0 .. ntile - 1; the band table last
-  int run = 0;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const int i = i0 + lane;
-    const bool has = i < n;
-    const int h = has ? tab[i].h : 0, w = has ? tab[i].w : 0;
-    for (int t = 0; t <= ntile; ++t) {
+  for (int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); t <= ntile; t += kSetupWaves) {
+    // tile prefix for class t / n_oct, octave t % n_oct
+    const int cls = t / p.n_oct, k = t - cls * p.n_oct;
+    int* out = t < ntile ? hp.tile_prefix + (cls * kMaxOct + k) * (n + 1) : hp.band_prefix;
+    int run = 0;
+    if (lane == 0) out[0] = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+      const int i = i0 + lane;
       int v = 0;
-      int* out;
-      if (t < ntile) {
-        // tile prefix for class t / n_oct, octave t % n_oct
-        const int cls = t / p.n_oct, k = t - cls * p.n_oct;
-        if (has) {
+      if (i < n) {
+        const int h = tab[i].h, w = tab[i].w;
+        if (t < ntile) {
           int hk, wk;
           octave_dims(h, w, p.upsample, k, &hk, &wk);
           v = cdiv(wk, kTileW) * cdiv(hk, tile_h_of(cls));
+        } else {
+          v = region_tail(h, w, lc).total_bands;
         }
-        out = hp.tile_prefix + (cls * kMaxOct + k) * (n + 1);
-      } else {
-        if (has) v = region_tail(h, w, lc).total_bands;
-        out = hp.band_prefix;
       }
       const int incl = wave_incl_scan(v);
-      const int base = __shfl(run, t, 64);
-      if (i0 == 0 && lane == 0) out[0] = 0;
-      if (has) out[i + 1] = base + incl;
-      const int chunk = __shfl(incl, 63, 64);
-      if (lane == t) run += chunk;
+      if (i < n) out[i + 1] = run + incl;
+      run += __shfl(incl, 63, 64);
     }
   }
-  // the work counters of this launch sequence
-  if (lane < min(n, kQueues)) *work_counter(hp, lane) = 0;
+  // the counters of this launch sequence
+  if (threadIdx.x < min(n, kQueues)) *work_counter(hp, tab, threadIdx.x) = 0;
+  if (threadIdx.x == 64) *images_done(hp) = 0;
+}
+
+__global__ __launch_bounds__(64 * kSetupWaves) void k_setup(HdrPtrs hp, SetupChunk c) {
+  const int t = threadIdx.x;
+  if (t < c.count) const_cast<ImgEntry*>(hp.table)[c.first + t] = c.e[t];
+  if (c.n > 0) prefix_tables(hp, c.e, c.n, c.p);
+}
+
+__global__ __launch_bounds__(64 * kSetupWaves) void k_finalize(HdrPtrs hp, int n, DevParams p) {
+  prefix_tables(hp, hp.table, n, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -303,9 +305,23 @@ __global__ __launch_bounds__(256) void k_band_scan(char* ws, HdrPtrs hp, int n, 
 // Candidate emission: one wave per (image, octave, band) writes the set bits
 // of its mask words, layer by layer, row by row, segment by segment, at the
 // offsets of the band scan -- the canonical (octave, layer, row, column) order.
+// The first work-group sums the images' candidates for the kernels that follow (as a
+// launch of its own 4.6 us).
 __global__ __launch_bounds__(64) void k_emit(char* ws, HdrPtrs hp, int n, DevParams p) {
+  if (blockIdx.x == 0) {
+    int base = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+      const int i = i0 + threadIdx.x;
+      const int v = i < n ? min(counters_of(ws, hp.table[i])[kCntCand], p.max_cand) : 0;
+      const int incl = wave_incl_scan(v);
+      if (i < n) hp.cand_prefix[i] = base + incl - v;
+      base += __shfl(incl, 63, 64);
+    }
+    if (threadIdx.x == 0) hp.cand_prefix[n] = base;
+    return;
+  }
   const int* bp = hp.band_prefix;
-  const int item = blockIdx.x;
+  const int item = blockIdx.x - 1;
   if (item >= bp[n]) return;
   const int img = find_owner(bp, n, item);
   const int lb = item - bp[img];
@@ -352,32 +368,6 @@ __global__ __launch_bounds__(64) void k_emit(char* ws, HdrPtrs hp, int n, DevPar
       base += __shfl(incl, 63, 64);
     }
   }
-}
-
-// Per-image prefix of min(counter, limit) over the batch (one work-group).
-__global__ __launch_bounds__(256) void k_img_prefix(char* ws, HdrPtrs hp, int n, DevParams p,
-                                                    int which) {
-  __shared__ int s_wave[4];
-  int* out = which == 0 ? hp.cand_prefix : hp.kp_prefix;
-  const ImgEntry* tab = hp.table;
-  int base = 0;
-  for (int c0 = 0; c0 < n; c0 += 256) {
-    const int i = c0 + threadIdx.x;
-    int v = 0;
-    if (i < n) {
-      const int* cnt = counters_of(ws, tab[i]);
-      if (which == 0) {
-        v = min(cnt[kCntCand], p.max_cand);
-      } else {
-        v = min(min(cnt[kCntKp], p.max_kp), tab[i].cap);
-      }
-    }
-    int tot;
-    const int ex = block_excl_scan256(v, s_wave, &tot);
-    if (i < n) out[i] = base + ex;
-    base += tot;
-  }
-  if (threadIdx.x == 0) out[n] = base;
 }
 
 // ---------------------------------------------------------------------------
@@ -556,7 +546,7 @@ struct WorkRuns {
   }
   __device__ __forceinline__ void ask() {
     run = min(max(left / (4 * waves), 1), 16);
-    if ((threadIdx.x & 63) == 0) ticket = atomicAdd(work_counter(hp, q), run);
+    if ((threadIdx.x & 63) == 0) ticket = atomicAdd(work_counter(hp, hp.table, q), run);
   }
   // the next item, or total when there is none
   __device__ __forceinline__ int pop() {
@@ -745,6 +735,7 @@ __global__ __launch_bounds__(256) void k_orient(char* ws, HdrPtrs hp, int n, Dev
 // image.  Publishes n_found and count.
 __global__ __launch_bounds__(256) void k_ori_scan(char* ws, HdrPtrs hp, int n, DevParams p) {
   __shared__ int s_wave[4];
+  __shared__ int s_last;
   const ImgEntry e = hp.table[blockIdx.x];
   const RegionTail rt = region_tail(e.h, e.w, layout_cfg(p));
   int* cnt = counters_of(ws, e);
@@ -771,7 +762,34 @@ __global__ __launch_bounds__(256) void k_ori_scan(char* ws, HdrPtrs hp, int n, D
     cnt[kCntKp] = base;
     if (e.n_found) *e.n_found = base;
     *e.count = min(min(base, p.max_kp), e.cap);
+    if (n > 1) {
+      __threadfence();
+      s_last = atomicAdd(images_done(hp), 1) == n - 1;
+    } else {
+      hp.kp_prefix[0] = 0;
+      hp.kp_prefix[1] = min(min(base, p.max_kp), e.cap);
+      s_last = 0;
+    }
   }
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  base = 0;
+  for (int c0 = 0; c0 < n; c0 += 256) {
+    const int i = c0 + threadIdx.x;
+    int v = 0;
+    if (i < n) {
+      const ImgEntry o = hp.table[i];
+      const int kp = __hip_atomic_load(&counters_of(ws, o)[kCntKp], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+      v = min(min(kp, p.max_kp), o.cap);
+    }
+    int tot;
+    const int ex = block_excl_scan256(v, s_wave, &tot);
+    if (i < n) hp.kp_prefix[i] = base + ex;
+    base += tot;
+  }
+  if (threadIdx.x == 0) hp.kp_prefix[n] = base;
 }
 
 // ---------------------------------------------------------------------------
@@ -1190,11 +1208,11 @@ void k_describe(char* ws, HdrPtrs hp, int n, DevParams p) {
 // Launch helpers
 
 hipError_t launch_setup(const HdrPtrs& hp, const SetupChunk& c, hipStream_t stream) {
-  return launch(k_setup, dim3(1), dim3(64), stream, hp, c);
+  return launch(k_setup, dim3(1), dim3(64 * kSetupWaves), stream, hp, c);
 }
 
 hipError_t launch_finalize(const HdrPtrs& hp, int n, const DevParams& p, hipStream_t stream) {
-  return launch(k_finalize, dim3(1), dim3(64), stream, hp, n, p);
+  return launch(k_finalize, dim3(1), dim3(64 * kSetupWaves), stream, hp, n, p);
 }
 
 hipError_t launch_detect(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int waves,
@@ -1221,12 +1239,7 @@ hipError_t launch_band_scan(char* ws, const HdrPtrs& hp, int n, const DevParams&
 
 hipError_t launch_emit(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream) {
-  return launch(k_emit, dim3(grid), dim3(64), stream, ws, hp, n, p);
-}
-
-hipError_t launch_img_prefix(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int which,
-                             hipStream_t stream) {
-  return launch(k_img_prefix, dim3(1), dim3(256), stream, ws, hp, n, p, which);
+  return launch(k_emit, dim3(grid + 1), dim3(64), stream, ws, hp, n, p);
 }
 
 hipError_t launch_refine(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,

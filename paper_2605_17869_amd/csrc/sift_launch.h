@@ -10,10 +10,13 @@ namespace sift {
 struct SetupChunk {
   int first;
   int count;
+  int n;                 // images of the batch if these are all of them, else 0
+  DevParams p;           // n > 0: the batch's settings
   ImgEntry e[kSetupChunk];
 };
 
 // Each helper enqueues one kernel on `stream` and returns the launch status.
+// Table entries; with c.n > 0 what launch_finalize does, too.
 hipError_t launch_setup(const HdrPtrs& hp, const SetupChunk& c, hipStream_t stream);
 hipError_t launch_finalize(const HdrPtrs& hp, int n, const DevParams& p, hipStream_t stream);
 // Gaussian level: `radius` selects the instantiation; taps in a.taps[0..2R].
@@ -31,9 +34,6 @@ hipError_t launch_band_scan(char* ws, const HdrPtrs& hp, int n, const DevParams&
                          hipStream_t stream);
 hipError_t launch_emit(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream);
-// Per-image prefix of min(counter, limit) into the header (which = 0 candidates, 1 keypoints).
-hipError_t launch_img_prefix(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int which,
-                             hipStream_t stream);
 hipError_t launch_refine(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream);
 hipError_t launch_orient(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
