@@ -371,7 +371,7 @@ __global__ __launch_bounds__(64) void k_emit(char* ws, HdrPtrs hp, int n, DevPar
 }
 
 // ---------------------------------------------------------------------------
-// Refinement: one thread per candidate, in double precision on the fp32 DoG
+// Refinement: one lane per candidate, in double precision on the fp32 DoG
 // samples.  Up to refine_iters Newton steps of the 3-D quadratic fit (the
 // 3x3 system solved by Cramer's rule); a step is final when all |x^| <= 0.5,
 // otherwise each coordinate with |x^| > 0.5 moves by x^ rounded half away
@@ -388,12 +388,55 @@ __device__ __forceinline__ double round_half_away(double x) {
   return x >= 0.0 ? floor(x + 0.5) : -floor(-x + 0.5);
 }
 
-__global__ __launch_bounds__(256) void k_refine(char* ws, HdrPtrs hp, int n, DevParams p) {
+// The samples of D that the fit reads around (r, c) of layer li: all of the middle
+// layer, the centre and its four neighbours of the outer two.  Every load is sent
+// before the first is used.
+template <bool H16>
+__device__ __forceinline__ void dog_samples(double (&d)[3][3][3], char* ws, const ImgEntry& e,
+                                            const OctView& ov, int li, int r, int c,
+                                            const Span& rs) {
+  float l[4][3][3];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const float* L = level_ptr(ws, e, ov, li - 1 + a);
+#pragma unroll
+    for (int dr = 0; dr < 3; ++dr)
+#pragma unroll
+      for (int dc = 0; dc < 3; ++dc) {
+        if ((a == 0 || a == 3) && dr != 1 && dc != 1) continue;
+        const int64_t off = (int64_t)(r - 1 + dr) * ov.pitch + (c - 1 + dc);
+        SIFT_CHECK_IN(rs, reinterpret_cast<const char*>(L) + off * (H16 ? 2 : 4), H16 ? 2 : 4);
+        l[a][dr][dc] = lv_at<H16>(L, off);
+      }
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int dr = 0; dr < 3; ++dr)
+#pragma unroll
+      for (int dc = 0; dc < 3; ++dc)
+        if (a == 1 || dr == 1 || dc == 1) d[a][dr][dc] = (double)(l[a + 1][dr][dc] - l[a][dr][dc]);
+}
+
+// Candidates are dealt to the waves 8 to 64 at a time, so that about kRefineWaves
+// of them (one per SIMD) have work: a load instruction's lanes read as many cache
+// lines, one after the other, and waves of one CU share that path.  Bound: the
+// latency of up to refine_iters rounds of loads and divisions.  480 x 640: 27 us with
+// work-groups of 256 candidates and each sample's loads under a branch of their own,
+// 12 now; 64 images of 768 x 1024, upsampled: 70 and 36.5; 512 or 2048 waves, or 4
+// candidates at least, make no difference beyond 1 us.
+// H16MODE: fp16 level storage is on; each candidate's octave picks the path.
+constexpr int kRefineWaves = 1024;
+
+template <bool H16MODE>
+__global__ __launch_bounds__(64) void k_refine(char* ws, HdrPtrs hp, int n, DevParams p) {
   const int* cp = hp.cand_prefix;
   const int total = cp[n];
   const ImgEntry* tab = hp.table;
   const LayoutCfg lc = layout_cfg(p);
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < total; g += gridDim.x * blockDim.x) {
+  const int each = min(max(cdiv(total, kRefineWaves), 8), 64);
+  if ((int)threadIdx.x >= each) return;
+  for (int g = blockIdx.x * each + threadIdx.x; g < total; g += gridDim.x * each) {
     const int img = find_owner(cp, n, g);
     const int j = g - cp[img];
     const ImgEntry e = tab[img];
@@ -403,7 +446,7 @@ __global__ __launch_bounds__(256) void k_refine(char* ws, HdrPtrs hp, int n, Dev
     const int k = cd.x;
     int li = cd.y, r = cd.z, c = cd.w;
     const OctView ov = octave_view(e.h, e.w, lc, k);
-    const int hk = ov.h, wk = ov.w, pk = ov.pitch;
+    const int hk = ov.h, wk = ov.w;
     const int b = p.border, s = p.s;
     RefinedKp out;
     out.ok = 0;
@@ -419,21 +462,10 @@ __global__ __launch_bounds__(256) void k_refine(char* ws, HdrPtrs hp, int n, Dev
     for (int it = 0; it < p.refine_iters; ++it) {
       // D samples of layers li-1, li, li+1 around (r, c)
       double d[3][3][3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const float* La = level_ptr(ws, e, ov, li - 1 + a);
-        const float* Lb = level_ptr(ws, e, ov, li + a);
-        const bool h16 = ov.es == 2;
-#pragma unroll
-        for (int dr = 0; dr < 3; ++dr)
-#pragma unroll
-          for (int dc = 0; dc < 3; ++dc) {
-            const int64_t off = (int64_t)(r - 1 + dr) * pk + (c - 1 + dc);
-            SIFT_CHECK_IN(rspan, reinterpret_cast<const char*>(La) + off * (h16 ? 2 : 4), h16 ? 2 : 4);
-            SIFT_CHECK_IN(rspan, reinterpret_cast<const char*>(Lb) + off * (h16 ? 2 : 4), h16 ? 2 : 4);
-            d[a][dr][dc] = (double)(lv_at(Lb, off, h16) - lv_at(La, off, h16));
-          }
-      }
+      if (H16MODE && ov.es == 2)
+        dog_samples<true>(d, ws, e, ov, li, r, c, SIFT_SPAN_VALUE(rspan));
+      else
+        dog_samples<false>(d, ws, e, ov, li, r, c, SIFT_SPAN_VALUE(rspan));
       v = d[1][1][1];
       gx = (d[1][1][2] - d[1][1][0]) * 0.5;
       gy = (d[1][2][1] - d[1][0][1]) * 0.5;
@@ -1244,7 +1276,9 @@ hipError_t launch_emit(char* ws, const HdrPtrs& hp, int n, const DevParams& p, i
 
 hipError_t launch_refine(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream) {
-  return launch(k_refine, dim3(grid), dim3(256), stream, ws, hp, n, p);
+  grid *= 4;   // groups of one wave
+  return p.h16 ? launch(k_refine<true>, dim3(grid), dim3(64), stream, ws, hp, n, p)
+               : launch(k_refine<false>, dim3(grid), dim3(64), stream, ws, hp, n, p);
 }
 
 hipError_t launch_orient(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
