@@ -482,7 +482,7 @@ namespace {
 struct Plan {
   std::vector<int64_t> tiles;   // blur strips x chunks, [octave * kNumTileH + chunk class]
   std::vector<int64_t> pixels;  // pixels per octave
-  std::vector<int64_t> oct_tiles;  // whole-octave tiles, [octave * 2 + tile width]
+  std::vector<int64_t> oct_tiles;  // whole-octave tiles, [octave * kOctTileClasses + class]
   int64_t input_px = 0;
   int64_t bands = 0;
 };
@@ -491,7 +491,7 @@ void plan_add(Plan* pl, const DevParams& p, int height, int width, int64_t times
   if (pl->tiles.empty()) {
     pl->tiles.assign((size_t)kNumTileH * p.n_oct, 0);
     pl->pixels.assign(p.n_oct, 0);
-    pl->oct_tiles.assign((size_t)2 * p.n_oct, 0);
+    pl->oct_tiles.assign((size_t)kOctTileClasses * p.n_oct, 0);
   }
   for (int k = 0; k < p.n_oct; ++k) {
     int hk, wk;
@@ -499,8 +499,9 @@ void plan_add(Plan* pl, const DevParams& p, int height, int width, int64_t times
     for (int c = 0; c < kNumTileH; ++c)
       pl->tiles[k * kNumTileH + c] += times * cdiv(wk, kTileW) * cdiv(hk, tile_h_of(c));
     pl->pixels[k] += times * (int64_t)hk * wk;
-    for (int c = 0; c < 2; ++c)
-      pl->oct_tiles[2 * k + c] += times * (int64_t)cdiv(wk, kOctTileW[c]) * cdiv(hk, kOctTileH);
+    for (int c = 0; c < kOctTileClasses; ++c)
+      pl->oct_tiles[kOctTileClasses * k + c] +=
+          times * (int64_t)cdiv(wk, kOctTileW[c]) * cdiv(hk, kOctTileH[c]);
   }
   pl->input_px += times * (int64_t)height * width;
   pl->bands += times * region_tail(height, width, layout_cfg(p)).total_bands;
@@ -604,10 +605,12 @@ sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, co
       const int st_mode = es_d == 4 ? 0 : (es_s == 4 ? 1 : 2);
       int nl = 1;
       int radii[kMaxScales + 3] = {};
-      // an octave of one round of tiles in one launch (the narrower tiles if they fit)
-      const int wide = plan.oct_tiles[2 * k] > kOctaveTiles;
+      // an octave of one round of tiles in one launch, of the smallest tiles that fit
+      const int64_t* oct_tiles = &plan.oct_tiles[kOctTileClasses * k];
+      int oct = 0;
+      while (oct < kOctTileClasses - 1 && oct_tiles[oct] > kOctaveTiles) ++oct;
       if (first_lv == lv && max_chain == kDefaultChain && n <= kOctMaxImages &&
-          plan.oct_tiles[2 * k + wide] <= kOctaveTiles && p.s + 3 - lv <= kOctMaxLevels) {
+          oct_tiles[oct] <= kOctaveTiles && p.s + 3 - lv <= kOctMaxLevels) {
         const int m = p.s + 3 - lv;
         for (int i = 0; i < m; ++i) radii[i] = taps_of(lv + i).radius;
         if (m > kChainMaxLevels && chain_supported(mode, st_mode, m, radii)) nl = m;
@@ -675,8 +678,8 @@ sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, co
           for (int q = 0; q <= t.radius; ++q) a.g[i][q] = t.g[t.radius + q];
         }
         const bool whole = nl > kChainMaxLevels;
-        if (whole) a.th = kOctTileW[wide];
-        const int groups = whole ? (int)plan.oct_tiles[2 * k + wide] : grid;
+        if (whole) a.th = kOctTileW[oct];
+        const int groups = whole ? (int)oct_tiles[oct] : grid;
         if (groups > 0 && (st = check_hip(launch_chain(a, mode, st_mode, nl, radii, groups, stream),
                                         "blur chain")) != SIFT_OK)
           return st;

@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kBlurThreads, 2) void k_chain(ChainArgs a) {
 
 // ---------------------------------------------------------------------------
 // A whole octave in one launch, for octaves of so few pixels that a launch's
-// time is the time of one work-group: per tile of TX x 32 pixels one work-group
+// time is the time of one work-group: per tile of TX x TY pixels one work-group
 // loads the source region that all levels together reach (radii 5, 7, 8, 10, 13:
 // 43 pixels on every side) and blurs it level after level in LDS, each level's
 // region smaller by its radius.  The tile's pixels of every level are stored.  The
@@ -562,12 +562,13 @@ __global__ __launch_bounds__(kBlurThreads, 2) void k_chain(ChainArgs a) {
 // with neighbouring lanes on neighbouring columns, horizontally on neighbouring
 // rows of odd pitch, both without bank conflicts.
 //
-// Bound: latency.  The region costs 5 times the operations of separate launches
-// (7 us of a CU's vector issue per 32 x 32 tile), which an idle chip has to spare:
-// a later octave takes 19 us instead of 44 in four launches of 8 to 17 us.  A tile
-// needs a CU's LDS to itself, so a launch is worth one round of tiles; wider
-// tiles (30 us instead of 24) hold the first octave of a 640x480 image to one.
-template <int TX, int... Rs>
+// Bound: latency.  The region costs many times the operations of separate launches
+// (a 32 x 32 tile 7 us of a CU's vector issue and 4 of its LDS), which an idle chip
+// has to spare: a later octave takes 19 us instead of 44 in four launches of 8 to
+// 17 us, and 16 in tiles of 16 x 16.  A tile needs a CU's LDS to itself, so a launch
+// is worth one round of tiles; wider tiles (30 us instead of 24) hold the first
+// octave of a 640x480 image to one.
+template <int TX, int TY, int... Rs>
 struct OctGeom {
   static constexpr int N = sizeof...(Rs);
   static constexpr int r(int i) {
@@ -581,19 +582,19 @@ struct OctGeom {
     return s;
   }
   static constexpr int cols(int i) { return TX + 2 * halo(i); }   // of level i's region
-  static constexpr int rows(int i) { return kOctTileH + 2 * halo(i); }
+  static constexpr int rows(int i) { return TY + 2 * halo(i); }
   static constexpr int src_halo() { return halo(0) + r(0); }
   static constexpr int src_cols() { return TX + 2 * src_halo(); }
-  static constexpr int src_rows() { return kOctTileH + 2 * src_halo(); }
+  static constexpr int src_rows() { return TY + 2 * src_halo(); }
 };
 
 constexpr int kOctThreads = 1024;
 constexpr int kOctRun = 8;   // outputs per task
 
-template <int TX, int MODE, int ST, int... Rs>
+template <int TX, int TY, int MODE, int ST, int... Rs>
 __global__ __launch_bounds__(kOctThreads) void k_octave(ChainArgs a) {
-  using Geo = OctGeom<TX, Rs...>;
-  constexpr int N = Geo::N, TY = kOctTileH, RUN = kOctRun, NT = kOctThreads;
+  using Geo = OctGeom<TX, TY, Rs...>;
+  constexpr int N = Geo::N, RUN = kOctRun, NT = kOctThreads;
   constexpr bool UP = MODE == kSrcUpsample;
   constexpr bool D16 = ST >= 1;
   constexpr uint32_t ES_D = D16 ? 2u : 4u;
@@ -771,12 +772,12 @@ struct ChainEntry {
   {M, S, 3, {5, 7, 8, 0}, k_chain<M, S, 5, 7, 8>},                             \
   {M, S, 2, {5, 7, 0, 0}, k_chain<M, S, 5, 7>}
 
-#define SIFT_OCTAVES(TX)                                                                        \
-  {kSrcUpsample, 0, 6, {5, 5, 7, 8, 10, 13}, k_octave<TX, kSrcUpsample, 0, 5, 5, 7, 8, 10, 13>, TX}, \
-  {kSrcImage, 0, 6, {7, 5, 7, 8, 10, 13}, k_octave<TX, kSrcImage, 0, 7, 5, 7, 8, 10, 13>, TX},       \
-  {kSrcDown, 0, 5, {5, 7, 8, 10, 13}, k_octave<TX, kSrcDown, 0, 5, 7, 8, 10, 13>, TX},               \
-  {kSrcDown, 1, 5, {5, 7, 8, 10, 13}, k_octave<TX, kSrcDown, 1, 5, 7, 8, 10, 13>, TX},               \
-  {kSrcDown, 2, 5, {5, 7, 8, 10, 13}, k_octave<TX, kSrcDown, 2, 5, 7, 8, 10, 13>, TX}
+#define SIFT_OCTAVES(TX, TY)                                                                       \
+  {kSrcUpsample, 0, 6, {5, 5, 7, 8, 10, 13}, k_octave<TX, TY, kSrcUpsample, 0, 5, 5, 7, 8, 10, 13>, TX}, \
+  {kSrcImage, 0, 6, {7, 5, 7, 8, 10, 13}, k_octave<TX, TY, kSrcImage, 0, 7, 5, 7, 8, 10, 13>, TX},       \
+  {kSrcDown, 0, 5, {5, 7, 8, 10, 13}, k_octave<TX, TY, kSrcDown, 0, 5, 7, 8, 10, 13>, TX},               \
+  {kSrcDown, 1, 5, {5, 7, 8, 10, 13}, k_octave<TX, TY, kSrcDown, 1, 5, 7, 8, 10, 13>, TX},               \
+  {kSrcDown, 2, 5, {5, 7, 8, 10, 13}, k_octave<TX, TY, kSrcDown, 2, 5, 7, 8, 10, 13>, TX}
 
 static const ChainEntry kChains[] = {
     {kSrcUpsample, 0, 4, {5, 5, 7, 8}, k_chain<kSrcUpsample, 0, 5, 5, 7, 8>},
@@ -792,8 +793,9 @@ static const ChainEntry kChains[] = {
     SIFT_CHAIN_ST(kSrcLevel, 2),
     {kSrcLevel, 0, 2, {7, 8, 0, 0}, k_chain<kSrcLevel, 0, 7, 8>},
     {kSrcLevel, 2, 2, {7, 8, 0, 0}, k_chain<kSrcLevel, 2, 7, 8>},
-    SIFT_OCTAVES(32),
-    SIFT_OCTAVES(48),
+    SIFT_OCTAVES(16, 16),
+    SIFT_OCTAVES(32, 32),
+    SIFT_OCTAVES(48, 32),
 };
 #undef SIFT_CHAIN_ST
 #undef SIFT_OCTAVES

@@ -311,8 +311,9 @@ constexpr int kChainMaxR = 8;
 // Whole octaves (k_octave): rows and the two widths of a tile, most levels,
 // largest radius, most images of a launch (a work-group finds its image with one
 // wave scan).
-constexpr int kOctTileH = 32;
-constexpr int kOctTileW[2] = {32, 48};
+constexpr int kOctTileClasses = 3;
+constexpr int kOctTileW[kOctTileClasses] = {16, 32, 48};
+constexpr int kOctTileH[kOctTileClasses] = {16, 32, 32};
 constexpr int kOctMaxLevels = 6;
 constexpr int kOctMaxR = 13;
 constexpr int kOctMaxImages = 64;
