@@ -50,7 +50,7 @@ constexpr int kBlurTargetGroups = 2048;
 constexpr int kDefaultChain = 2;
 // Tiles up to which an octave is taken whole in one launch: one per CU.  With 768
 // tiles (the last octave of 64 1024x768 images, 12 each) a launch took 66 us against
-// 63 in four, with 300 46 against 51, with up to 256 19 to 24 against 44 to 51.
+// 63 in four, with 300 46 against 51, with up to 256 16 to 24 against 44 to 51.
 constexpr int64_t kOctaveTiles = 256;
 
 int blur_class(int tile_rows, const int64_t* tiles_of_class) {

@@ -1,5 +1,5 @@
 """Octaves of few pixels taken whole in one launch against one launch per level:
-levels and features bit-identical in both tile widths, at tile edges, for images
+levels and features bit-identical in every tile size, at tile edges, for images
 smaller than the halo, fp16 storage and batches up to the launch's image limit.
 Needs an MI355X."""
 import pytest
