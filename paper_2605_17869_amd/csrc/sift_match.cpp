@@ -141,6 +141,7 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
   char* ws = static_cast<char*>(d_workspace);
   MatchHdr h;
+  std::memset(&h, 0, sizeof h);
   h.ws = ws;
   h.table = reinterpret_cast<const MatchEntry*>(ws + L.table);
   h.row_prefix = reinterpret_cast<int*>(ws + L.row_prefix);
@@ -162,28 +163,37 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
     return fail(SIFT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
   };
   hipError_t e;
-  for (int first = 0; first < n; first += kMatchSetupChunk) {
+  auto entry = [&](int i) {
+    const sift_match_pair& q = pairs[i];
+    MatchEntry m;
+    std::memset(&m, 0, sizeof m);
+    m.desc_a = q.desc_a;
+    m.count_a = q.count_a;
+    m.desc_b = q.desc_b;
+    m.count_b = q.count_b;
+    m.matches = q.matches;
+    m.n_matches = q.n_matches;
+    m.n_found = q.n_found;
+    m.cap_a = q.cap_a;
+    m.cap_b = q.cap_b;
+    m.capacity = q.capacity;
+    m.best = L.best[i];
+    m.part = L.part[i];
+    m.half = L.half[i];
+    return m;
+  };
+  h.carried = n <= kMatchOwnPairs ? 1 : 0;
+  for (int i = 0; h.carried && i <= n; ++i) {
+    h.rows[i] = rp[i];
+    h.cols[i] = cp[i];
+    if (i < n) h.e[i] = entry(i);
+  }
+  for (int first = 0; !h.carried && first < n; first += kMatchSetupChunk) {
     MatchSetupChunk c;
     std::memset(&c, 0, sizeof c);
     c.first = first;
     c.count = std::min(kMatchSetupChunk, n - first);
-    for (int t = 0; t < c.count; ++t) {
-      const sift_match_pair& q = pairs[first + t];
-      MatchEntry& m = c.e[t];
-      m.desc_a = q.desc_a;
-      m.count_a = q.count_a;
-      m.desc_b = q.desc_b;
-      m.count_b = q.count_b;
-      m.matches = q.matches;
-      m.n_matches = q.n_matches;
-      m.n_found = q.n_found;
-      m.cap_a = q.cap_a;
-      m.cap_b = q.cap_b;
-      m.capacity = q.capacity;
-      m.best = L.best[first + t];
-      m.part = L.part[first + t];
-      m.half = L.half[first + t];
-    }
+    for (int t = 0; t < c.count; ++t) c.e[t] = entry(first + t);
     for (int t = 0; t <= c.count; ++t) {
       c.row_prefix[t] = rp[first + t];
       c.col_prefix[t] = cp[first + t];

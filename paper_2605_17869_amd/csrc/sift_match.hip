@@ -82,12 +82,14 @@ __device__ __forceinline__ half8 load_half8(const float* row, int k, bool valid)
   return h;
 }
 
-__global__ void k_match_setup(MatchHdr h, MatchSetupChunk c, int n) {
+// Calls of more pairs than the kernels carry in their arguments.
+__global__ void k_match_setup(MatchEntry* table, int* row_prefix, int* col_prefix,
+                              MatchSetupChunk c, int n) {
   const int t = threadIdx.x;
-  if (t < c.count) const_cast<MatchEntry*>(h.table)[c.first + t] = c.e[t];
+  if (t < c.count) table[c.first + t] = c.e[t];
   if (t <= c.count && c.first + t <= n) {
-    h.row_prefix[c.first + t] = c.row_prefix[t];
-    h.col_prefix[c.first + t] = c.col_prefix[t];
+    row_prefix[c.first + t] = c.row_prefix[t];
+    col_prefix[c.first + t] = c.col_prefix[t];
   }
 }
 
@@ -105,6 +107,12 @@ __device__ __forceinline__ _Float16* half_of(const MatchHdr& h, const MatchEntry
   return reinterpret_cast<_Float16*>(h.ws + e.half) + (b_side ? (int64_t)e.cap_a * kMatchDim : 0);
 }
 
+// Entry of pair p.
+__device__ __forceinline__ MatchEntry entry_of(const MatchHdr& h, int p) {
+  if (h.carried) return h.e[p];
+  return h.table[p];
+}
+
 // Pair of a row tile and the tile's number within it.  Pairs of equal tile
 // counts need no search: its dependent loads were a third of a work-group's time
 // before its first product.
@@ -112,6 +120,13 @@ __device__ __forceinline__ int pair_of_tile(const MatchHdr& h, int n, int tile, 
   if (h.same_tiles) {
     const int p = tile / h.same_tiles;
     *local = tile - p * h.same_tiles;
+    return p;
+  }
+  if (h.carried) {
+    int p = 0;
+    for (int step = kMatchOwnPairs / 2; step >= 1; step /= 2)
+      if (p + step < n && h.rows[p + step] <= tile) p += step;
+    *local = tile - h.rows[p];
     return p;
   }
   const int p = __builtin_amdgcn_readfirstlane(find_owner(h.row_prefix, n, tile));
@@ -123,7 +138,7 @@ __device__ __forceinline__ int pair_of_tile(const MatchHdr& h, int n, int tile, 
 __global__ __launch_bounds__(256) void k_match_half(MatchHdr h, int n) {
   int local;
   const int p = pair_of_tile(h, n, blockIdx.x, &local);
-  const MatchEntry e = h.table[p];
+  const MatchEntry e = entry_of(h, p);
   const int at = (e.cap_a + h.own_rows - 1) / h.own_rows;
   const int b_side = local >= at;
   const int row0 = (b_side ? local - at : local) * h.own_rows;
@@ -181,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int ti
   const int chunk = item % h.chunks, tile = item / h.chunks;
   int local;
   const int p = pair_of_tile(h, n, tile, &local);
-  const MatchEntry e = h.table[p];
+  const MatchEntry e = entry_of(h, p);
   const int at = (e.cap_a + kOwn - 1) / kOwn;
   const int b_side = local >= at;   // own rows are b's
   const int row0 = (b_side ? local - at : local) * kOwn;
@@ -348,9 +363,18 @@ __device__ __forceinline__ Top2 best_at(const MatchHdr& h, const MatchEntry& e, 
 
 // Merge of the chunks, one thread per row of either set.
 __global__ __launch_bounds__(kMatchMergeBlock) void k_match_merge(MatchHdr h, int n) {
-  const int p = find_owner(h.col_prefix, n, blockIdx.x);
-  const MatchEntry e = h.table[p];
-  int i = (blockIdx.x - h.col_prefix[p]) * kMatchMergeBlock + threadIdx.x;
+  const int block = blockIdx.x;
+  int p = 0, first;
+  if (h.carried) {
+    for (int step = kMatchOwnPairs / 2; step >= 1; step /= 2)
+      if (p + step < n && h.cols[p + step] <= block) p += step;
+    first = h.cols[p];
+  } else {
+    p = find_owner(h.col_prefix, n, block);
+    first = h.col_prefix[p];
+  }
+  const MatchEntry e = entry_of(h, p);
+  int i = (block - first) * kMatchMergeBlock + threadIdx.x;
   const int b_side = i >= e.cap_a;
   if (b_side) i -= e.cap_a;
   if (i >= (b_side ? rows_in_use(e.count_b, e.cap_b) : rows_in_use(e.count_a, e.cap_a))) return;
@@ -376,7 +400,7 @@ constexpr int kEmitThreads = 1024, kEmitRows = 8;
 __global__ __launch_bounds__(kEmitThreads) void k_match_emit(MatchHdr h, int n, float ratio_sq) {
   constexpr int kCounts = kEmitRows * kEmitThreads / 64;   // one per 64 rows
   __shared__ int s_cnt[kCounts], s_wave[4];
-  const MatchEntry e = h.table[blockIdx.x];
+  const MatchEntry e = entry_of(h, blockIdx.x);
   const int na = rows_in_use(e.count_a, e.cap_a);
   const int nb = rows_in_use(e.count_b, e.cap_b);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -445,7 +469,8 @@ __global__ __launch_bounds__(kEmitThreads) void k_match_emit(MatchHdr h, int n, 
 
 hipError_t launch_match_setup(const MatchHdr& h, const MatchSetupChunk& c, int n,
                               hipStream_t stream) {
-  return launch(k_match_setup, dim3(1), dim3(64), stream, h, c, n);
+  return launch(k_match_setup, dim3(1), dim3(64), stream, const_cast<MatchEntry*>(h.table),
+                h.row_prefix, h.col_prefix, c, n);
 }
 
 hipError_t launch_match_rows(const MatchHdr& h, int n, int grid, hipStream_t stream) {
