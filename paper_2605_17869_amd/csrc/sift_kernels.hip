@@ -307,9 +307,37 @@ __global__ __launch_bounds__(256) void k_band_scan(char* ws, HdrPtrs hp, int n, 
 // offsets of the band scan -- the canonical (octave, layer, row, column) order.
 // The first work-group sums the images' candidates for the kernels that follow (as a
 // launch of its own 4.6 us).
+// SCAN: no band scan has run.  A wave then sums the counts before its band itself, and
+// the first work-group every image's: worth it while the bands are few
+// (kScanInEmitBands), where the scan's launch takes longer than the sums.
+__device__ __forceinline__ int wave_sum_i(int v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+
+template <bool SCAN>
 __global__ __launch_bounds__(64) void k_emit(char* ws, HdrPtrs hp, int n, DevParams p) {
   if (blockIdx.x == 0) {
     int base = 0;
+    if (SCAN) {
+      for (int i = 0; i < n; ++i) {
+        const ImgEntry e = hp.table[i];
+        const RegionTail rt = region_tail(e.h, e.w, layout_cfg(p));
+        const int* bc = reinterpret_cast<const int*>(ws + e.region + rt.band_cnt);
+        int v = 0;
+        for (int q = threadIdx.x; q < rt.total_bands * p.s; q += 64) v += bc[q];
+        v = wave_sum_i(v);
+        if (threadIdx.x == 0) {
+          counters_of(ws, e)[kCntCand] = v;
+          if (e.n_cand) *e.n_cand = v;
+          hp.cand_prefix[i] = base;
+        }
+        base += min(v, p.max_cand);
+      }
+      if (threadIdx.x == 0) hp.cand_prefix[n] = base;
+      return;
+    }
     for (int i0 = 0; i0 < n; i0 += 64) {
       const int i = i0 + threadIdx.x;
       const int v = i < n ? min(counters_of(ws, hp.table[i])[kCntCand], p.max_cand) : 0;
@@ -342,8 +370,25 @@ __global__ __launch_bounds__(64) void k_emit(char* ws, HdrPtrs hp, int n, DevPar
   const int* bo = reinterpret_cast<const int*>(ws + e.region + rt.band_off);
   int4* cands = reinterpret_cast<int4*>(ws + e.region + rt.cands);
   const int lane = threadIdx.x;
+  const int slot = ov.band_base * p.s + band;   // of layer 1; a layer's are nband apart
+  int before = 0;   // SCAN: lane i, candidates before this band's of layer i + 1
+  if (SCAN) {
+    int sum[kMaxScales] = {};
+    const int* bc = reinterpret_cast<const int*>(ws + e.region + rt.band_cnt);
+    for (int q = lane; q < slot + (p.s - 1) * ov.nband; q += 64) {
+      const int v = bc[q];
+#pragma unroll
+      for (int i = 0; i < kMaxScales; ++i) sum[i] += q < slot + i * ov.nband ? v : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kMaxScales; ++i)
+      if (i < p.s) {
+        const int all = wave_sum_i(sum[i]);
+        before = lane == i ? all : before;
+      }
+  }
   for (int i = 1; i <= p.s; ++i) {
-    int base = bo[ov.band_base * p.s + (i - 1) * ov.nband + band];
+    int base = SCAN ? __shfl(before, i - 1, 64) : bo[slot + (i - 1) * ov.nband];
     for (int w0 = 0; w0 < nwords; w0 += 64) {
       const int wi = w0 + lane;
       unsigned long long m = 0ull;
@@ -1284,7 +1329,9 @@ hipError_t launch_band_scan(char* ws, const HdrPtrs& hp, int n, const DevParams&
 
 hipError_t launch_emit(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream) {
-  return launch(k_emit, dim3(grid + 1), dim3(64), stream, ws, hp, n, p);
+  return grid <= kScanInEmitBands
+             ? launch(k_emit<true>, dim3(grid + 1), dim3(64), stream, ws, hp, n, p)
+             : launch(k_emit<false>, dim3(grid + 1), dim3(64), stream, ws, hp, n, p);
 }
 
 hipError_t launch_refine(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
