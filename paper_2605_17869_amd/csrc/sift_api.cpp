@@ -704,7 +704,7 @@ sift_status launch_stages(const sift_handle* h, const Config& cfg, int32_t n, co
     return st;
   prof_end(prec, stream);
   prec = prof_begin(kStCompact, (p.s / 4.0) * all_px, stream);
-  if (bands > kScanInEmitBands &&
+  if (!scan_in_emit(bands, n) &&
       (st = check_hip(launch_band_scan(ws, hp, n, p, stream), "band scan")) != SIFT_OK)
     return st;
   if ((st = check_hip(launch_emit(ws, hp, n, p, bands, stream), "emit")) != SIFT_OK) return st;

@@ -308,8 +308,8 @@ __global__ __launch_bounds__(256) void k_band_scan(char* ws, HdrPtrs hp, int n, 
 // The first work-group sums the images' candidates for the kernels that follow (as a
 // launch of its own 4.6 us).
 // SCAN: no band scan has run.  A wave then sums the counts before its band itself, and
-// the first work-group every image's: worth it while the bands are few
-// (kScanInEmitBands), where the scan's launch takes longer than the sums.
+// the first work-group every image's, one after the other: worth it while bands and
+// images are few (scan_in_emit), where the scan's launch takes longer than the sums.
 __device__ __forceinline__ int wave_sum_i(int v) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
@@ -1329,7 +1329,7 @@ hipError_t launch_band_scan(char* ws, const HdrPtrs& hp, int n, const DevParams&
 
 hipError_t launch_emit(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream) {
-  return grid <= kScanInEmitBands
+  return scan_in_emit(grid, n)
              ? launch(k_emit<true>, dim3(grid + 1), dim3(64), stream, ws, hp, n, p)
              : launch(k_emit<false>, dim3(grid + 1), dim3(64), stream, ws, hp, n, p);
 }

@@ -32,10 +32,16 @@ hipError_t launch_detect(char* ws, const HdrPtrs& hp, int n, const DevParams& p,
                          int grid, hipStream_t stream);
 hipError_t launch_band_scan(char* ws, const HdrPtrs& hp, int n, const DevParams& p,
                          hipStream_t stream);
-// Up to this many bands launch_emit (whose grid they are) does the band scan's work: one
-// 480 x 640 image (110 bands) 170.2 -> 167.2 us, 97 x 131 145.2 -> 142.3; with thousands
-// each wave's sum over all counts before it takes longer than the scan (28 -> 36 us).
-constexpr int kScanInEmitBands = 512;
+// Whether launch_emit, whose grid are the bands, does the band scan's work.  Its first
+// work-group then sums the images' counts one image after the other, about 1 us each, and
+// every wave the counts before its band.  One 480 x 640 image (110 bands) 170.2 us with a
+// scan's launch, 167.2 without; 97 x 97 images (19 bands each): 1 139 and 137, 4 151 and
+// 149, 6 157.7 and 158.5, 16 in each of four sequences 482 and 509.  With thousands of
+// bands a wave's sum takes longer than the scan (28 -> 36 us).
+constexpr int kScanInEmitBands = 512, kScanInEmitImages = 4;
+inline bool scan_in_emit(int bands, int n) {
+  return bands <= kScanInEmitBands && n <= kScanInEmitImages;
+}
 hipError_t launch_emit(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
                          hipStream_t stream);
 hipError_t launch_refine(char* ws, const HdrPtrs& hp, int n, const DevParams& p, int grid,
