@@ -1,5 +1,5 @@
 // Host runtime of descriptor matching: argument checks, workspace layout and
-// the launch sequence (setup, nearest neighbours, merge of chunks, emission).
+// the launch sequence (setup, nearest neighbours, merge of parts, emission).
 // Like extraction, it never allocates device memory, copies or synchronises.
 #include <hip/hip_runtime.h>
 
@@ -31,7 +31,7 @@ int cdiv_i(int a, int b) { return (a + b - 1) / b; }
 struct MatchLayout {
   int64_t table, row_prefix, col_prefix;
   std::vector<int64_t> best, part, half;
-  int chunks = 1;   // parts of a walk over the other set
+  std::vector<int> parts_a, parts_b;   // parts of the walks over the other set
   int own_rows = kMatchTile;
   bool half_copies = false, merge = false;
   int64_t bytes;
@@ -65,12 +65,18 @@ constexpr int64_t kMatchTargetGroups = 512;
 // is staged so few times that a launch of its own costs more than converting
 // it again (one pair of 2000 x 2000: 256 tiles; 8192 x 7900: 3968).
 constexpr int64_t kMatchHalfTiles = 1024;
-// Rows of a pair's sets up to which the emission merges the chunks itself.
+// ... and only where a tile of the sets is staged that often on average: a copy moves
+// 6 bytes per value to save 2 of 4 each time the value is read.  With and without
+// copies, us: 1000 pairs of 500 x 500 (4 stagings) 485 and 468, 100 of 640 x 640 (5) 85
+// and 73, 100 of 700 x 700 (6) 93 and 91, one of 65536 x 500 (8) 256 and 266.
+constexpr int64_t kMatchHalfStagings = 7;
+// Rows of a pair's sets up to which the emission merges the parts itself.
 constexpr int64_t kMatchEmitMergeRows = 2048;
 
-// The plan of a call and its workspace.  `lean`: no chunks and no copies, the
-// least a call can run in.
-MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool lean) {
+// The plan of a call and its workspace.  `half`: the sets are copied to fp16 first where
+// that pays; `stretch`: parts of walks are that many times longer than would be best (0:
+// no parts at all).  Without copies and parts a call runs in the least memory.
+MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool half, int stretch) {
   MatchLayout L;
   int64_t off = 0;
   L.table = off;
@@ -79,37 +85,58 @@ MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool lean) {
   off = align256(off + (int64_t)(n + 1) * 4);
   L.col_prefix = off;
   off = align256(off + (int64_t)(n + 1) * 4);
-  if (!lean) {
-    int64_t row_tiles = 0, tiles = 0;
-    int most_tiles = 0, most_rows = 0;
+  int64_t row_tiles = 0, tiles = 0;
+  int most_rows = 0;
+  for (int i = 0; i < n; ++i) {
+    const int ta = cdiv_i(pairs[i].cap_a, kMatchTile), tb = cdiv_i(pairs[i].cap_b, kMatchTile);
+    row_tiles += ta + tb;
+    tiles += (int64_t)ta * tb;
+    most_rows = std::max(most_rows, pairs[i].cap_a + pairs[i].cap_b);
+  }
+  L.half_copies =
+      half && tiles >= kMatchHalfTiles && 2 * tiles >= kMatchHalfStagings * row_tiles;
+  if (L.half_copies) L.own_rows = kMatchOwnHalf;
+  int walk = SIFT_MATCH_MAX_ROWS;   // tiles of a part
+  if (stretch > 0) {
+    // A walk is cut where it is longer than every group's share of all tiles, be it that
+    // the call has few groups (8192 x 7900 without parts: 63 of them) or that one set is
+    // much longer than the other (65536 x 100: 512 walks of one tile and one of 512, 1264
+    // us while only the number of groups was looked at, 252 now; 32 pairs of 4096 x 128
+    // 128 and 56).
+    int64_t steps = 0;
     for (int i = 0; i < n; ++i) {
-      const int ta = cdiv_i(pairs[i].cap_a, kMatchTile), tb = cdiv_i(pairs[i].cap_b, kMatchTile);
-      row_tiles += ta + tb;
-      tiles += (int64_t)ta * tb;
-      most_tiles = std::max(most_tiles, std::max(ta, tb));
-      most_rows = std::max(most_rows, pairs[i].cap_a + pairs[i].cap_b);
+      const int64_t ca = pairs[i].cap_a, cb = pairs[i].cap_b;
+      steps += (int64_t)cdiv_i(ca, L.own_rows) * cdiv_i(cb, kMatchTile) +
+               (int64_t)cdiv_i(cb, L.own_rows) * cdiv_i(ca, kMatchTile);
     }
-    L.half_copies = tiles >= kMatchHalfTiles;
-    if (L.half_copies) {
-      L.own_rows = kMatchOwnHalf;
-      row_tiles = 0;
-      for (int i = 0; i < n; ++i)
-        row_tiles += cdiv_i(pairs[i].cap_a, L.own_rows) + cdiv_i(pairs[i].cap_b, L.own_rows);
-    }
-    const int64_t want = row_tiles > 0 ? (kMatchTargetGroups + row_tiles - 1) / row_tiles : 1;
-    L.chunks = (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min(most_tiles, kMatchMaxChunks)));
-    L.merge = L.chunks > 1 && most_rows > kMatchEmitMergeRows;
+    walk = (int)std::min<int64_t>(std::max<int64_t>(steps / kMatchTargetGroups, 1) * stretch, walk);
   }
   for (int i = 0; i < n; ++i) {
     const int64_t rows = (int64_t)pairs[i].cap_a + pairs[i].cap_b;
     L.best.push_back(off);
     off = align256(off + rows * (int64_t)sizeof(Top2));
     L.part.push_back(off);
-    if (L.chunks > 1) off = align256(off + rows * L.chunks * (int64_t)sizeof(Top2));
+    const int pa = match_parts(walk, pairs[i].cap_b), pb = match_parts(walk, pairs[i].cap_a);
+    L.parts_a.push_back(pa);
+    L.parts_b.push_back(pb);
+    L.merge = L.merge || ((pa > 1 || pb > 1) && most_rows > kMatchEmitMergeRows);
+    const int64_t kept = (pa > 1 ? (int64_t)pa * pairs[i].cap_a : 0) +
+                         (pb > 1 ? (int64_t)pb * pairs[i].cap_b : 0);
+    off = align256(off + kept * (int64_t)sizeof(Top2));
     L.half.push_back(off);
     if (L.half_copies) off = align256(off + rows * 128 * 2);
   }
   L.bytes = off;
+  return L;
+}
+
+// The best plan that fits: the one sift_match_workspace_size reports, then without
+// copies, then with longer parts, then without parts.
+MatchLayout layout_within(int32_t n, const sift_match_pair* pairs, int64_t bytes) {
+  MatchLayout L = layout_of(n, pairs, true, 1);
+  for (int stretch = 1; L.bytes > bytes && stretch <= kMatchMaxParts; stretch *= 2)
+    L = layout_of(n, pairs, false, stretch);
+  if (L.bytes > bytes) L = layout_of(n, pairs, false, 0);
   return L;
 }
 
@@ -121,7 +148,7 @@ sift_status sift_match_workspace_size(int32_t n, const sift_match_pair* pairs, s
   if (!bytes) return fail(SIFT_ERR_INVALID_ARG, "null bytes");
   sift_status st = check_pairs(n, pairs);
   if (st != SIFT_OK) return st;
-  *bytes = (size_t)layout_of(n, pairs, false).bytes;
+  *bytes = (size_t)layout_of(n, pairs, true, 1).bytes;
   return SIFT_OK;
 }
 
@@ -133,8 +160,7 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   if (!d_workspace) return fail(SIFT_ERR_INVALID_ARG, "null workspace");
   if (reinterpret_cast<uintptr_t>(d_workspace) % 256)
     return fail(SIFT_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-  MatchLayout L = layout_of(n, pairs, false);
-  if ((int64_t)workspace_bytes < L.bytes) L = layout_of(n, pairs, true);
+  const MatchLayout L = layout_within(n, pairs, (int64_t)workspace_bytes);
   if ((int64_t)workspace_bytes < L.bytes)
     return fail(SIFT_ERR_WORKSPACE_TOO_SMALL, "workspace " + std::to_string(workspace_bytes) +
                                                   " bytes, need " + std::to_string(L.bytes));
@@ -146,19 +172,19 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   h.table = reinterpret_cast<const MatchEntry*>(ws + L.table);
   h.row_prefix = reinterpret_cast<int*>(ws + L.row_prefix);
   h.col_prefix = reinterpret_cast<int*>(ws + L.col_prefix);
-  h.chunks = L.chunks;
-  h.half = L.half_copies ? 1 : 0;
   h.merged = 0;
   h.own_rows = L.own_rows;
 
   std::vector<int> rp(n + 1, 0), cp(n + 1, 0);
   for (int i = 0; i < n; ++i) {
-    rp[i + 1] = rp[i] + cdiv_i(pairs[i].cap_a, L.own_rows) + cdiv_i(pairs[i].cap_b, L.own_rows);
+    rp[i + 1] = rp[i] + cdiv_i(pairs[i].cap_a, L.own_rows) * L.parts_a[i] +
+                cdiv_i(pairs[i].cap_b, L.own_rows) * L.parts_b[i];
     cp[i + 1] = cp[i] + cdiv_i(pairs[i].cap_a + pairs[i].cap_b, kMatchMergeBlock);
   }
-  h.same_tiles = rp[1];
+  h.half = L.half_copies ? cp[n] : 0;
+  h.same_items = rp[1];
   for (int i = 1; i < n; ++i)
-    if (rp[i + 1] - rp[i] != rp[1]) h.same_tiles = 0;
+    if (rp[i + 1] - rp[i] != rp[1]) h.same_items = 0;
   auto hip_fail = [](hipError_t e, const char* what) {
     return fail(SIFT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
   };
@@ -177,6 +203,8 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
     m.cap_a = q.cap_a;
     m.cap_b = q.cap_b;
     m.capacity = q.capacity;
+    m.parts_a = (int16_t)L.parts_a[i];
+    m.parts_b = (int16_t)L.parts_b[i];
     m.best = L.best[i];
     m.part = L.part[i];
     m.half = L.half[i];

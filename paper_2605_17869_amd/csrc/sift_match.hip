@@ -97,11 +97,22 @@ __global__ void k_match_setup(MatchEntry* table, int* row_prefix, int* col_prefi
 __device__ __forceinline__ Top2* best_of(const MatchHdr& h, const MatchEntry& e, int b_side) {
   return reinterpret_cast<Top2*>(h.ws + e.best) + (b_side ? e.cap_a : 0);
 }
+// Parts of the walks of that set's rows over the other set.
+__device__ __forceinline__ int parts_of(const MatchEntry& e, int b_side) {
+  return b_side ? e.parts_b : e.parts_a;
+}
+// v / parts for 0 <= v < 2^13, the same for every lane: v + 1/2 over at most 8 is 1 / 16 or
+// more from a whole number, far more than the error of its product.
+static_assert(kMatchMaxParts <= 8 && 2 * SIFT_MATCH_MAX_ROWS / kMatchTile * kMatchMaxParts <= 8192, "");
+__device__ __forceinline__ int parts_quotient(int v, int parts) {
+  return __builtin_amdgcn_readfirstlane(
+      (int)(((float)v + 0.5f) * __builtin_amdgcn_rcpf((float)parts)));
+}
 __device__ __forceinline__ Top2* part_of(const MatchHdr& h, const MatchEntry& e, int b_side,
-                                         int chunk) {
+                                         int part) {
+  const int64_t after_a = e.parts_a > 1 ? (int64_t)e.parts_a * e.cap_a : 0;
   return reinterpret_cast<Top2*>(h.ws + e.part) +
-         (b_side ? (int64_t)h.chunks * e.cap_a + (int64_t)chunk * e.cap_b
-                 : (int64_t)chunk * e.cap_a);
+         (b_side ? after_a + (int64_t)part * e.cap_b : (int64_t)part * e.cap_a);
 }
 __device__ __forceinline__ _Float16* half_of(const MatchHdr& h, const MatchEntry& e, int b_side) {
   return reinterpret_cast<_Float16*>(h.ws + e.half) + (b_side ? (int64_t)e.cap_a * kMatchDim : 0);
@@ -113,52 +124,72 @@ __device__ __forceinline__ MatchEntry entry_of(const MatchHdr& h, int p) {
   return h.table[p];
 }
 
-// Pair of a row tile and the tile's number within it.  Pairs of equal tile
-// counts need no search: its dependent loads were a third of a work-group's time
-// before its first product.
-__device__ __forceinline__ int pair_of_tile(const MatchHdr& h, int n, int tile, int* local) {
-  if (h.same_tiles) {
-    const int p = tile / h.same_tiles;
-    *local = tile - p * h.same_tiles;
+// Pair of a work item and the item's number within it.  Pairs of equally many need
+// no search: its dependent loads were a third of a work-group's time before its
+// first product.
+__device__ __forceinline__ int pair_of_item(const MatchHdr& h, int n, int item, int* local) {
+  if (h.same_items) {
+    const int p = item / h.same_items;
+    *local = item - p * h.same_items;
     return p;
   }
   if (h.carried) {
     int p = 0;
     for (int step = kMatchOwnPairs / 2; step >= 1; step /= 2)
-      if (p + step < n && h.rows[p + step] <= tile) p += step;
-    *local = tile - h.rows[p];
+      if (p + step < n && h.rows[p + step] <= item) p += step;
+    *local = item - h.rows[p];
     return p;
   }
-  const int p = __builtin_amdgcn_readfirstlane(find_owner(h.row_prefix, n, tile));
-  *local = tile - __builtin_amdgcn_readfirstlane(h.row_prefix[p]);
+  const int p = __builtin_amdgcn_readfirstlane(find_owner(h.row_prefix, n, item));
+  *local = item - __builtin_amdgcn_readfirstlane(h.row_prefix[p]);
   return p;
 }
 
-// The sets as fp16 (round to nearest even), one work-group per row tile.
+// Pair of a block of kMatchMergeBlock rows of its two sets, a's and then b's, and the
+// block's number within it.
+__device__ __forceinline__ int pair_of_rows(const MatchHdr& h, int n, int block, int* local) {
+  int p = 0;
+  if (h.carried) {
+    for (int step = kMatchOwnPairs / 2; step >= 1; step /= 2)
+      if (p + step < n && h.cols[p + step] <= block) p += step;
+    *local = block - h.cols[p];
+  } else {
+    p = find_owner(h.col_prefix, n, block);
+    *local = block - h.col_prefix[p];
+  }
+  return p;
+}
+
+// The sets as fp16 (round to nearest even), kMatchMergeBlock rows a work-group.
 __global__ __launch_bounds__(256) void k_match_half(MatchHdr h, int n) {
   int local;
-  const int p = pair_of_tile(h, n, blockIdx.x, &local);
+  const int p = pair_of_rows(h, n, blockIdx.x, &local);
   const MatchEntry e = entry_of(h, p);
-  const int at = (e.cap_a + h.own_rows - 1) / h.own_rows;
-  const int b_side = local >= at;
-  const int row0 = (b_side ? local - at : local) * h.own_rows;
-  const int rows = b_side ? rows_in_use(e.count_b, e.cap_b) : rows_in_use(e.count_a, e.cap_a);
-  const float* src = b_side ? e.desc_b : e.desc_a;
-  _Float16* dst = half_of(h, e, b_side);
-  for (int i = 0; i < h.own_rows * (kMatchDim / 8) / 256; ++i) {
-    const int piece = i * 256 + threadIdx.x;
-    const int row = row0 + piece / (kMatchDim / 8), k = piece % (kMatchDim / 8) * 8;
-    if (row < rows) {
-      SIFT_CHECK_INDEX(row, b_side ? e.cap_b : e.cap_a);
-      *reinterpret_cast<half8*>(dst + (int64_t)row * kMatchDim + k) =
-          load_half8(src + (int64_t)row * kMatchDim, k, true);
+  const int first = local * kMatchMergeBlock;
+  for (int b_side = 0; b_side < 2; ++b_side) {
+    // the block's rows of this set
+    const int off = b_side ? e.cap_a : 0, cap = b_side ? e.cap_b : e.cap_a;
+    const int row0 = max(first - off, 0);
+    if (row0 >= cap || first + kMatchMergeBlock <= off) continue;
+    const int end = min(first + kMatchMergeBlock - off, rows_in_use(b_side ? e.count_b : e.count_a, cap));
+    const float* src = b_side ? e.desc_b : e.desc_a;
+    _Float16* dst = half_of(h, e, b_side);
+#pragma unroll
+    for (int i = 0; i < kMatchMergeBlock * (kMatchDim / 8) / 256; ++i) {
+      const int piece = i * 256 + threadIdx.x;
+      const int row = row0 + piece / (kMatchDim / 8), k = piece % (kMatchDim / 8) * 8;
+      if (row < end) {
+        SIFT_CHECK_INDEX(row, cap);
+        *reinterpret_cast<half8*>(dst + (int64_t)row * kMatchDim + k) =
+            load_half8(src + (int64_t)row * kMatchDim, k, true);
+      }
     }
   }
 }
 
 // ---------------------------------------------------------------------------
 // Nearest neighbours.  One work-group (4 waves) per (pair, set, tile of 32 OB
-// rows of that set, its own rows, chunk of the other set); it walks the chunk's
+// rows of that set, its own rows, part of the other set); it walks the part's
 // tiles of 128 rows.  Waves 2 h and 2 h + 1 hold half h of the own rows as
 // MFMA B operands in registers for the whole walk and take the two halves of
 // each tile, which is staged in LDS as fp16 (two buffers: the next tile is on
@@ -181,7 +212,7 @@ __global__ __launch_bounds__(256) void k_match_half(MatchHdr h, int n) {
 // Eight read half of LDS and memory per product that four do (83 against 96
 // us), four make twice the work-groups of a small call.
 template <bool HALF, int OB>
-__global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int tiles) {
+__global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int items) {
   // HALF: a tile is copied to LDS by the load unit, rows unpadded, the 16-byte
   // pieces of row r at places p ^ (r % 16) (the 16 rows a wave reads together
   // then lie in different banks)
@@ -192,14 +223,17 @@ __global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int ti
   // neighbouring items (one pair's tiles) to one XCD, whose L2 then holds the pair
   const int per_xcd = gridDim.x / kXcds;
   const int item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-  if (item >= tiles * h.chunks) return;
-  const int chunk = item % h.chunks, tile = item / h.chunks;
+  if (item >= items) return;
   int local;
-  const int p = pair_of_tile(h, n, tile, &local);
+  const int p = pair_of_item(h, n, item, &local);
   const MatchEntry e = entry_of(h, p);
-  const int at = (e.cap_a + kOwn - 1) / kOwn;
-  const int b_side = local >= at;   // own rows are b's
-  const int row0 = (b_side ? local - at : local) * kOwn;
+  const int a_items = (e.cap_a + kOwn - 1) / kOwn * e.parts_a;
+  const int b_side = local >= a_items;   // own rows are b's
+  const int parts = parts_of(e, b_side);
+  if (b_side) local -= a_items;
+  // a tile's parts follow each other
+  const int tile = parts_quotient(local, parts), part = local - tile * parts;
+  const int row0 = tile * kOwn;
   const int na = __builtin_amdgcn_readfirstlane(rows_in_use(e.count_a, e.cap_a));
   const int nb = __builtin_amdgcn_readfirstlane(rows_in_use(e.count_b, e.cap_b));
   const int n_own = b_side ? nb : na, n_oth = b_side ? na : nb;
@@ -217,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int ti
     if (HALF) return *reinterpret_cast<const half8*>(hs + at);
     return load_half8(fs + at, 0, true);
   };
-  // own fragments: row row0 + 64 own_half + 16 tb + li, k = 32 kk + 8 gq (rows past
+  // own fragments: row row0 + 16 OB own_half + 16 tb + li, k = 32 kk + 8 gq (rows past
   // the set's end repeat the last one; nothing of theirs is stored)
   half8 fb[OB][4];
 #pragma unroll
@@ -266,9 +300,9 @@ __global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int ti
         *reinterpret_cast<half8*>(&buf[(kPieceRows * i + prow) * kStride + pk]) = st[i];
     }
   };
-  // the chunk's tiles of the other set, from the rows in use
+  // the part's tiles of the other set, from the rows in use
   const int used = (n_oth + kMatchTile - 1) / kMatchTile;
-  const int c0 = used * chunk / h.chunks, c1 = used * (chunk + 1) / h.chunks;
+  const int c0 = parts_quotient(used * part, parts), c1 = parts_quotient(used * (part + 1), parts);
   // one tile: TAIL, the last one, has rows past the set's end
   auto walk = [&](auto tail, const _Float16* buf, int ct) {
     constexpr bool TAIL = decltype(tail)::value;
@@ -348,36 +382,30 @@ __global__ __launch_bounds__(256, 2) void k_match_best(MatchHdr h, int n, int ti
   __syncthreads();
   if (t < kOwn && row0 + t < n_own) {
     SIFT_CHECK_INDEX(row0 + t, cap_own);
-    Top2* out = h.chunks == 1 ? best_of(h, e, b_side) : part_of(h, e, b_side, chunk);
+    Top2* out = parts == 1 ? best_of(h, e, b_side) : part_of(h, e, b_side, part);
     out[row0 + t] = top2_merge(s_part[0][t], s_part[1][t]);
   }
 }
 
-// The nearest over all chunks of row i of one set.
+// The nearest over all parts of row i of one set.
 __device__ __forceinline__ Top2 best_at(const MatchHdr& h, const MatchEntry& e, int b_side, int i) {
-  if (h.chunks == 1 || h.merged) return best_of(h, e, b_side)[i];
+  const int parts = parts_of(e, b_side);
+  if (parts == 1 || h.merged) return best_of(h, e, b_side)[i];
   Top2 c = part_of(h, e, b_side, 0)[i];
-  for (int q = 1; q < h.chunks; ++q) c = top2_merge(c, part_of(h, e, b_side, q)[i]);
+  for (int q = 1; q < parts; ++q) c = top2_merge(c, part_of(h, e, b_side, q)[i]);
   return c;
 }
 
-// Merge of the chunks, one thread per row of either set.
+// Merge of the parts, one thread per row of either set.
 __global__ __launch_bounds__(kMatchMergeBlock) void k_match_merge(MatchHdr h, int n) {
-  const int block = blockIdx.x;
-  int p = 0, first;
-  if (h.carried) {
-    for (int step = kMatchOwnPairs / 2; step >= 1; step /= 2)
-      if (p + step < n && h.cols[p + step] <= block) p += step;
-    first = h.cols[p];
-  } else {
-    p = find_owner(h.col_prefix, n, block);
-    first = h.col_prefix[p];
-  }
+  int local;
+  const int p = pair_of_rows(h, n, blockIdx.x, &local);
   const MatchEntry e = entry_of(h, p);
-  int i = (block - first) * kMatchMergeBlock + threadIdx.x;
+  int i = local * kMatchMergeBlock + threadIdx.x;
   const int b_side = i >= e.cap_a;
   if (b_side) i -= e.cap_a;
   if (i >= (b_side ? rows_in_use(e.count_b, e.cap_b) : rows_in_use(e.count_a, e.cap_a))) return;
+  if (parts_of(e, b_side) == 1) return;   // one part is the whole walk
   SIFT_CHECK_INDEX(i, b_side ? e.cap_b : e.cap_a);
   best_of(h, e, b_side)[i] = best_at(h, e, b_side, i);
 }
@@ -475,10 +503,10 @@ hipError_t launch_match_setup(const MatchHdr& h, const MatchSetupChunk& c, int n
 
 hipError_t launch_match_rows(const MatchHdr& h, int n, int grid, hipStream_t stream) {
   if (h.half) {
-    const hipError_t e = launch(k_match_half, dim3(grid), dim3(256), stream, h, n);
+    const hipError_t e = launch(k_match_half, dim3(h.half), dim3(256), stream, h, n);
     if (e != hipSuccess) return e;
   }
-  const int items = (grid * h.chunks + kXcds - 1) / kXcds * kXcds;
+  const int items = (grid + kXcds - 1) / kXcds * kXcds;
   return launch(h.half ? k_match_best<true, kMatchOwnHalf / 32> : k_match_best<false, kMatchTile / 32>,
                 dim3(items), dim3(256), stream, h, n, grid);
 }

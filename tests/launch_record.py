@@ -10,9 +10,11 @@ ROOT = Path(__file__).resolve().parents[1]
 CSRC = ROOT / "paper_2605_17869_amd" / "csrc"
 
 FRAME = r"""
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <string>
 #include <vector>
 #include "sift_launch.h"
 #include "sift_match.h"
