@@ -118,6 +118,7 @@ sift_status sift_verify_batch(int32_t n, const sift_verify_pair* pairs, const fl
     std::memset(&c, 0, sizeof c);
     c.first = first;
     c.count = std::min(kVerifySetupChunk, n - first);
+    c.prepare = n <= kVerifySetupChunk;
     for (int t = 0; t < c.count; ++t) {
       const sift_verify_pair& q = pairs[first + t];
       VerifyEntry& v = c.e[t];
@@ -139,6 +140,8 @@ sift_status sift_verify_batch(int32_t n, const sift_verify_pair* pairs, const fl
     }
     if ((e = launch_verify_setup(hd, c, stream)) != hipSuccess) return hip_fail(e, "verify setup");
   }
+  if (n > kVerifySetupChunk && (e = launch_verify_prep(hd, n, stream)) != hipSuccess)
+    return hip_fail(e, "verify prep");
   if ((e = launch_verify_models(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify models");
   if ((e = launch_verify_hyp(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify hypotheses");
   if ((e = launch_verify_refine(hd, n, stream)) != hipSuccess) return hip_fail(e, "verify refine");

@@ -12,7 +12,7 @@
 
 namespace sift {
 
-constexpr int kVerifySetupChunk = 24;  // pairs per setup launch
+constexpr int kVerifySetupChunk = 24;  // pair-table entries per setup launch
 constexpr int kVerifyHypPerGroup = 4;  // hypotheses per work-group (one per wave)
 constexpr int kNormLargest = 6;        // where `norm` holds the largest coordinate
 constexpr int kVerifyModelBlock = 64;  // hypotheses per work-group of the model kernel (one per lane)
@@ -50,11 +50,13 @@ struct VerifyHdr {
 struct VerifySetupChunk {
   int first;
   int count;
+  int prepare;       // 1: the launch prepares the pairs' points, too
   VerifyEntry e[kVerifySetupChunk];
 };
 
-// table entries and points of the chunk's pairs
+// table entries of the chunk's pairs; with c.prepare what launch_verify_prep does, too
 hipError_t launch_verify_setup(const VerifyHdr& h, const VerifySetupChunk& c, hipStream_t stream);
+hipError_t launch_verify_prep(const VerifyHdr& h, int n, hipStream_t stream);
 hipError_t launch_verify_models(const VerifyHdr& h, int n, hipStream_t stream);
 hipError_t launch_verify_hyp(const VerifyHdr& h, int n, hipStream_t stream);
 hipError_t launch_verify_refine(const VerifyHdr& h, int n, hipStream_t stream);

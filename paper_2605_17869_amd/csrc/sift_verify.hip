@@ -306,22 +306,30 @@ __global__ __launch_bounds__(kVerifyModelBlock) void k_verify_models(VerifyHdr h
   for (int q = 0; q < 9; ++q) out[q] = ok ? H[q] : NAN;
 }
 
-// Per pair, one work-group: its table entry (from the kernel's arguments), the
-// matched points gathered (pixels), the normalising similarity of each set (mean
-// to 0, mean distance to sqrt 2) and the normalised points.  Sums run as 256
-// partial sums, partial sum v over correspondences v, v + 256, ..., whatever the
-// number of threads that gather.  Bound: the latency of its dependent loads: 7 us for
-// one pair of 211 matches, 11 for up to kVerifySetupChunk pairs of 1300; the table in
-// a launch of its own and a preparation by 256 threads took 10 and 16.
+__global__ void k_verify_setup(VerifyHdr hd, VerifySetupChunk c) {
+  const int t = threadIdx.x;
+  if (t < c.count) const_cast<VerifyEntry*>(hd.table)[c.first + t] = c.e[t];
+}
+
+// Per pair, one work-group: the matched points gathered (pixels), the normalising
+// similarity of each set (mean to 0, mean distance to sqrt 2) and the normalised points.
+// Sums run as 256 partial sums, partial sum v over correspondences v, v + 256, ...,
+// whatever the number of threads that gather.  Where the kernel's arguments hold every
+// pair (!TABLE), they bring the table entries, which it stores.  Bound: the latency
+// of its dependent loads: 7 us for one pair of 211 matches, 11 for 24 of 1300; the table
+// in a launch of its own and a preparation by 256 threads took 10 and 16.  More pairs
+// have their table written first, 24 a launch, and are prepared together: with a launch
+// of this kernel for every 24 pairs 1024 pairs of 50 matches took 313 us here, now 111.
 constexpr int kPrepThreads = 1024, kPrepHeld = 4096;   // threads; points kept in LDS
 
+template <bool TABLE>
 __global__ __launch_bounds__(kPrepThreads) void k_verify_prep(VerifyHdr hd, VerifySetupChunk c) {
   __shared__ double s4[4];
   __shared__ float4 s_raw[kPrepHeld];
   __shared__ float s_max[kPrepThreads / 64];
-  const VerifyEntry e = c.e[blockIdx.x];
+  const VerifyEntry e = TABLE ? hd.table[blockIdx.x] : c.e[blockIdx.x];
   const int t = threadIdx.x;
-  if (t == 0) const_cast<VerifyEntry*>(hd.table)[c.first + blockIdx.x] = e;
+  if (!TABLE && t == 0) const_cast<VerifyEntry*>(hd.table)[c.first + blockIdx.x] = e;
   const int n = verify_count(e);
   float4* raw = reinterpret_cast<float4*>(hd.ws + e.raw);
   double* pts = reinterpret_cast<double*>(hd.ws + e.pts);
@@ -760,7 +768,12 @@ __global__ __launch_bounds__(kRefineThreads) void k_verify_refine(VerifyHdr hd, 
 }
 
 hipError_t launch_verify_setup(const VerifyHdr& h, const VerifySetupChunk& c, hipStream_t stream) {
-  return launch(k_verify_prep, dim3(c.count), dim3(kPrepThreads), stream, h, c);
+  return c.prepare ? launch(k_verify_prep<false>, dim3(c.count), dim3(kPrepThreads), stream, h, c)
+                   : launch(k_verify_setup, dim3(1), dim3(64), stream, h, c);
+}
+
+hipError_t launch_verify_prep(const VerifyHdr& h, int n, hipStream_t stream) {
+  return launch(k_verify_prep<true>, dim3(n), dim3(kPrepThreads), stream, h, VerifySetupChunk{});
 }
 
 hipError_t launch_verify_models(const VerifyHdr& h, int n, hipStream_t stream) {
