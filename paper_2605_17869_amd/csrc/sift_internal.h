@@ -262,6 +262,23 @@ struct DevParams {
   float dsp[SIFT_MAX_DSP];
 };
 
+// Keypoints per work-group of the descriptor kernel up to which a keypoint's streams are
+// shared by the four waves.  A wave then waits where a window has fewer than four streams,
+// all the longer the more sizes a pixel is binned for; left to itself it waits for the work
+// counters.  Times of one image shared / a wave per keypoint, at 1.7, 2.4 and 3.5 keypoints a
+// group, us: one size 253 / 304, 316 / 349, 360 / 388; five sizes up to 2 342 / 470, 413 / 525,
+// 489 / 582; five up to 4/3 (windows of one and two streams) 321 / 364, 397 / 410, 475 / 453;
+// ten up to 4/3 380 / 407, 475 / 456, 581 / 506; 16 up to 4/3 499 / 461, 643 / 507, 855 / 676;
+// ten up to 4 610 / 1328, 953 / 1402, 1091 / 1571.
+SIFT_HD int desc_share_limit(float largest_window, int n_dsp) {
+  if (largest_window >= 20.0f || n_dsp <= 2) return 4;
+  return n_dsp <= 5 ? 3 : (n_dsp <= 10 ? 2 : 1);
+}
+// Half the side of the largest domain size's window at the smallest scale, in pixels.
+SIFT_HD float desc_largest_window(const DevParams& p) {
+  return 2.5f * p.desc_magnif * p.sigma0 * p.dsp[0];
+}
+
 SIFT_HD LayoutCfg layout_cfg(const DevParams& p) {
   LayoutCfg c;
   c.n_oct = p.n_oct;

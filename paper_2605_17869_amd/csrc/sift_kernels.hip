@@ -593,12 +593,6 @@ constexpr int kDescLdsPrefix = 319;
 // (one 640x480 image: 31, 35 and 35 us).
 constexpr int kDescOneStream = 81;
 constexpr int kDescTwoStreams = 169;
-// Keypoints per work-group up to which a keypoint's streams are shared by the
-// waves of a work-group.  8 images of 800x600 with five sizes (about 4,100
-// keypoints on 4096 waves): 0.46 ms with a wave per keypoint, 0.30 ms shared;
-// four times as many keypoints fill the waves either way.
-constexpr int kDescShareLimit = 4;
-
 // Work items of a wave, out of `total` for the launch.  The items are split
 // evenly over up to kQueues counters; a work-group starts at the counter of its
 // XCD (work-groups are dealt to the XCDs in turn) and goes on to the others when
@@ -974,7 +968,7 @@ void k_describe(char* ws, HdrPtrs hp, int n, DevParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* const hist = s_hist[wave];
   WorkRuns runs(hp, n, total);
-  const bool shared_kp = total <= kDescShareLimit * (int)gridDim.x;
+  const bool shared_kp = total <= desc_share_limit(desc_largest_window(p), p.n_dsp) * (int)gridDim.x;
   int g = shared_kp ? (int)blockIdx.x : runs.pop();
   while (g < total) {
     // the next keypoint, fetched while this one runs
