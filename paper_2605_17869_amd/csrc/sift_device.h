@@ -129,23 +129,35 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// The larger and the smaller magnitude; of a number and a NaN the number, as fmaxf and
+// fminf, which would first make each operand canonical, an instruction each.
+__device__ __forceinline__ float max_abs(float a, float b) {
+  float d;
+  __asm__("v_max_f32 %0, |%1|, |%2|" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ float min_abs(float a, float b) {
+  float d;
+  __asm__("v_min_f32 %0, |%1|, |%2|" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
 // Gradient orientation atan2(y, x) in (-pi, pi]: octant reduction to
 // a = min(|x|, |y|) / max(|x|, |y|) and atan(a) = a * P(a^2), a degree-7
 // polynomial fitted by weighted least squares (csrc/fit_atan.py; maximum
-// error 1.4e-7 rad in fp32).  atan2(0, 0) = 0.
+// error 1.4e-7 rad in fp32).  atan2(0, 0) = 0; a NaN counts as as large as the other
+// component and positive, two as 0.
 __device__ __forceinline__ float atan2_poly(float y, float x) {
   constexpr float c[8] = {0.999999344f, -0.333298594f, 0.199465662f, -0.139086306f,
                           0.0964219868f, -0.0559123345f, 0.0218629558f, -0.00405456498f};
-  const float ax = fabsf(x), ay = fabsf(y);
-  const bool steep = ay > ax;
-  const float mx = steep ? ay : ax, mn = steep ? ax : ay;
+  const float mx = max_abs(x, y), mn = min_abs(x, y);
   const float a = mx > 0.0f ? mn * __builtin_amdgcn_rcpf(mx) : 0.0f;
   const float s = a * a;
   float r = c[7];
 #pragma unroll
   for (int j = 6; j >= 0; --j) r = __fmaf_rn(r, s, c[j]);
   r = r * a;
-  if (steep) r = 1.57079632679489662f - r;
+  if (fabsf(y) > fabsf(x)) r = 1.57079632679489662f - r;
   if (x < 0.0f) r = 3.14159265358979324f - r;
   return y < 0.0f ? -r : r;
 }
