@@ -409,9 +409,10 @@ __global__ __launch_bounds__(kPrepThreads) void k_verify_prep(VerifyHdr hd, Veri
 // (entries of H rounded, two fused steps) are within 4 u X, 4 u Y, 4 u W, and
 // ex = x - bx w within 5.1 u (X + C W).  Its test means |(ex, ey)| < L w with
 // L = tau smax (1 + 5e-10), so the computed values satisfy |(ex, ey)| < L w + K,
-// K = 4 u L W + 5.1 u (X + Y + 2 C W); K is taken with 8 u (and a floor far above the
-// smallest numbers), the comparison of squares with 1e-6 to spare.  The conditions are
-// written so that NaN and infinity pass.
+// K = 4 u L W + 5.1 u (X + Y + 2 C W); K is taken with 8 u, the comparison of squares
+// with 1e-6 to spare, and K with a floor whose square is a normal number (below those,
+// roundings are no longer relative).  The conditions are written so that NaN and
+// infinity pass.
 struct Admit32 {
   float h[9], L, K;
   __device__ __forceinline__ Admit32(const double* H, double smax, float C) {
@@ -421,7 +422,7 @@ struct Admit32 {
     const float X = C * (fabsf(h[0]) + fabsf(h[1])) + fabsf(h[2]);
     const float Y = C * (fabsf(h[3]) + fabsf(h[4])) + fabsf(h[5]);
     const float W = C * (fabsf(h[6]) + fabsf(h[7])) + fabsf(h[8]);
-    K = 4.76837158e-7f * (L * W + ((X + Y) + 2.0f * (C * W))) + 1e-25f;
+    K = 4.76837158e-7f * (L * W + ((X + Y) + 2.0f * (C * W))) + 1e-18f;
   }
   __device__ __forceinline__ bool operator()(const float4& p) const {
     const float x = __fmaf_rn(p.x, h[0], __fmaf_rn(p.y, h[1], h[2]));
