@@ -111,7 +111,9 @@ typedef struct {
                                  to that many consecutive levels of an octave blurred in one
                                  launch (runs of radius <= 8 that the library has a kernel
                                  for), so the levels between are not read back from memory;
-                                 0 and 2 also take octaves of few pixels whole in one launch.
+                                 0 and 2 also take octaves of few pixels whole in one launch
+                                 (default sigma0 and n_scales; nothing gives chains of two
+                                 alone).
                                  Any value gives bit-identical results (tuning only) */
   int32_t detect_waves;       /* 0: library choice (4); 4 or 8: waves per work-group of the
                                  extrema search, which share a band's column segments.
@@ -541,7 +543,8 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
  * Geometric verification of matched pairs: the estimator after matching
  * (Section 3.6, "GPU MAGSAC++": many minimal-sample hypotheses solved in one
  * batch, scored by soft marginalisation), as a planar homography, for many
- * pairs in one launch sequence.  All arithmetic is fp64.
+ * pairs in one launch sequence.  Every result is computed in fp64; single
+ * precision only passes over correspondences whose weight is 0 beyond doubt.
  *
  * For a pair, the correspondences are the first *n_matches records of
  * `matches` (sift_match_batch output: query indexes kp_a, train kp_b), their

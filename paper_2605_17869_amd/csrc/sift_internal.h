@@ -325,9 +325,10 @@ constexpr int kChainB = 16;
 constexpr int kChainMaxLevels = 4;
 constexpr int kChainMaxR = 8;
 
-// Whole octaves (k_octave): rows and the two widths of a tile, most levels,
+// Whole octaves (k_octave): widths and heights of the tile classes, most levels,
 // largest radius, most images of a launch (a work-group finds its image with one
-// wave scan).
+// wave scan).  Built for the radii of sigma0 = 1.6 with three scales per octave, the
+// default; other settings take their octaves level by level and in chains.
 constexpr int kOctTileClasses = 3;
 constexpr int kOctTileW[kOctTileClasses] = {16, 32, 48};
 constexpr int kOctTileH[kOctTileClasses] = {16, 32, 32};

@@ -85,12 +85,12 @@ __global__ __launch_bounds__(64 * kSetupWaves) void k_finalize(HdrPtrs hp, int n
 // neighbours.  The per-row result is a 64-bit ballot word per (layer, row, segment),
 // stored once per band; per-band counts feed the ordered compaction.
 //
-// Bound: memory for many images (64 of 768 x 1024, upsampled: 1.50 ms, 9.4 GB read,
-// of which 6.4 are the levels), for few the latency of the rows' loads, kDetAhead of
-// which are on their way: 480 x 640 takes 15.9 us, 17.9 with one row ahead, 25 with
-// none, and 27.8 with the rows' maxima in plain code (125 vector instructions a row
-// instead of 75).  Bands of two and four times the rows read fewer halo rows but
-// leave fewer waves: 1.52 and 1.64 ms, and 24 and 37 us.
+// Bound: memory for many images (64 of 768 x 1024, upsampled: 1.50 ms, 8.6 GB read,
+// of which 6.5 are the levels, 5.9 TB/s with what is written), for few the latency of
+// the rows' loads, kDetAhead of which are on their way: 480 x 640 takes 15.9 us, 17.9
+// with one row ahead, 25 with none, and 27.8 with the rows' maxima in plain code (125
+// vector instructions a row instead of 75).  Bands of two and four times the rows read
+// fewer halo rows but leave fewer waves: 1.52 and 1.64 ms, and 24 and 37 us.
 
 template <int S>
 struct DetRow {
@@ -945,6 +945,9 @@ constexpr int kHistWords = 2 * kHistRow2;
 
 // ND: the number of domain sizes the code is unrolled for (1, or the most).
 // H16MODE: fp16 level storage is on; each keypoint's octave picks the path.
+// Four waves per SIMD leave 128 registers: one size takes 99, five 117, ten would take
+// a few more and keep 24 bytes a lane in scratch, reloaded in the packing loop; 16
+// sizes (156) run three.
 template <int ND, bool H16MODE>
 __global__ __launch_bounds__(64 * kDescWaves)
 __attribute__((amdgpu_waves_per_eu(ND <= 10 ? 4 : 3)))

@@ -1,7 +1,8 @@
 // gfx950 kernels of geometric verification: homography hypotheses from
 // minimal samples, scored by the noise-scale-marginalised inlier likelihood,
-// the best one refined by reweighted least squares.  All arithmetic is fp64
-// (single precision only passes over terms that are zero beyond doubt); every sum runs in an order fixed by the code (per-lane partial sums in index
+// the best one refined by reweighted least squares.  Every result is computed in
+// fp64 (single precision only passes over terms that are zero beyond doubt), and
+// every sum runs in an order fixed by the code (per-lane partial sums in index
 // order, then a fixed butterfly and a fixed order over waves), so results are
 // bit-identical from run to run.  Built with -ffp-contract=off.
 #include <hip/hip_runtime.h>
