@@ -140,17 +140,6 @@ MatchLayout layout_within(int32_t n, const sift_match_pair* pairs, int64_t bytes
   return L;
 }
 
-// The least workspace a call takes (see include/sift.h): the nearest of every row and one
-// summary per b row and 128 a rows, or less where sift_match_workspace_size asks for less.
-int64_t least_bytes(int32_t n, const sift_match_pair* pairs) {
-  int64_t off = align256((int64_t)n * (int64_t)sizeof(MatchEntry)) + 2 * align256((int64_t)(n + 1) * 4);
-  for (int i = 0; i < n; ++i) {
-    const int64_t a = pairs[i].cap_a, b = pairs[i].cap_b;
-    off += align256(16 * a) + align256(16 * b) + align256(16 * b * cdiv_i((int)a, 128));
-  }
-  return std::min(off, layout_of(n, pairs, true, 1).bytes);
-}
-
 }  // namespace
 
 extern "C" {
@@ -172,10 +161,9 @@ sift_status sift_match_batch(int32_t n, const sift_match_pair* pairs, float rati
   if (reinterpret_cast<uintptr_t>(d_workspace) % 256)
     return fail(SIFT_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
   const MatchLayout L = layout_within(n, pairs, (int64_t)workspace_bytes);
-  const int64_t least = std::max(least_bytes(n, pairs), L.bytes);
-  if ((int64_t)workspace_bytes < least)
+  if ((int64_t)workspace_bytes < L.bytes)
     return fail(SIFT_ERR_WORKSPACE_TOO_SMALL, "workspace " + std::to_string(workspace_bytes) +
-                                                  " bytes, need " + std::to_string(least));
+                                                  " bytes, need " + std::to_string(L.bytes));
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
   char* ws = static_cast<char*>(d_workspace);
   MatchHdr h;
