@@ -504,9 +504,13 @@ sift_status sift_server_destroy(sift_server* s);
  * cap_a / cap_b rows; matches [capacity]; *n_matches receives the number
  * written (min(kept, capacity)), *n_found (may be NULL) the number kept.
  * Caps are host values that size the launch; 0 <= cap <= 65536.
- * sift_match_workspace_size gives the workspace for the pairs (host array);
- * sift_match_batch enqueues the matching on `stream` (no allocation, copy
- * or synchronisation).  Errors: INVALID_ARG for null pointers, caps out of
+ * sift_match_workspace_size gives the workspace for the pairs (host array).
+ * A smaller one is taken, too, down to the least: 96 n bytes, twice 4 n + 4, and
+ * for every pair 16 (cap_a + cap_b), each rounded up to 256.  The results are
+ * the same bits; a call that would have used more then takes longer (one pair of
+ * 8192 x 7900 in the least: 2.3 times as long).  Below the least:
+ * WORKSPACE_TOO_SMALL.  sift_match_batch enqueues the matching on `stream` (no
+ * allocation, copy or synchronisation).  Errors: INVALID_ARG for null pointers, caps out of
  * range, ratio not in (0, 1], WORKSPACE_TOO_SMALL; HIP for launch failures.
  */
 typedef struct {

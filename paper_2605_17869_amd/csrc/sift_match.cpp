@@ -74,9 +74,9 @@ constexpr int64_t kMatchHalfStagings = 7;
 constexpr int64_t kMatchEmitMergeRows = 2048;
 
 // The plan of a call and its workspace.  `half`: the sets are copied to fp16 first where
-// that pays; `stretch`: parts of walks are that many times longer than would be best (0:
-// no parts at all).  Without copies and parts a call runs in the least memory.
-MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool half, int stretch) {
+// that pays; `most`: parts that a walk may be cut into.  Without copies and in one part a
+// call runs in the least memory.
+MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool half, int most) {
   MatchLayout L;
   int64_t off = 0;
   L.table = off;
@@ -96,27 +96,26 @@ MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool half, int st
   L.half_copies =
       half && tiles >= kMatchHalfTiles && 2 * tiles >= kMatchHalfStagings * row_tiles;
   if (L.half_copies) L.own_rows = kMatchOwnHalf;
-  int walk = SIFT_MATCH_MAX_ROWS;   // tiles of a part
-  if (stretch > 0) {
-    // A walk is cut where it is longer than every group's share of all tiles, be it that
-    // the call has few groups (8192 x 7900 without parts: 63 of them) or that one set is
-    // much longer than the other (65536 x 100: 512 walks of one tile and one of 512, 1264
-    // us while only the number of groups was looked at, 252 now; 32 pairs of 4096 x 128
-    // 128 and 56).
-    int64_t steps = 0;
-    for (int i = 0; i < n; ++i) {
-      const int64_t ca = pairs[i].cap_a, cb = pairs[i].cap_b;
-      steps += (int64_t)cdiv_i(ca, L.own_rows) * cdiv_i(cb, kMatchTile) +
-               (int64_t)cdiv_i(cb, L.own_rows) * cdiv_i(ca, kMatchTile);
-    }
-    walk = (int)std::min<int64_t>(std::max<int64_t>(steps / kMatchTargetGroups, 1) * stretch, walk);
+  // A walk is cut where it is longer than every group's share of all tiles, be it that
+  // the call has few groups (8192 x 7900 without parts: 63 of them) or that one set is
+  // much longer than the other (65536 x 100: 512 walks of one tile and one of 512, 1264
+  // us while only the number of groups was looked at, 252 now; 32 pairs of 4096 x 128
+  // 128 and 56).
+  int64_t steps = 0;
+  for (int i = 0; i < n; ++i) {
+    const int ca = pairs[i].cap_a, cb = pairs[i].cap_b;
+    steps += (int64_t)cdiv_i(ca, L.own_rows) * cdiv_i(cb, kMatchTile) +
+             (int64_t)cdiv_i(cb, L.own_rows) * cdiv_i(ca, kMatchTile);
   }
+  const int walk = (int)std::min<int64_t>(std::max<int64_t>(steps / kMatchTargetGroups, 1),
+                                          SIFT_MATCH_MAX_ROWS);   // tiles of a part
   for (int i = 0; i < n; ++i) {
     const int64_t rows = (int64_t)pairs[i].cap_a + pairs[i].cap_b;
     L.best.push_back(off);
     off = align256(off + rows * (int64_t)sizeof(Top2));
     L.part.push_back(off);
-    const int pa = match_parts(walk, pairs[i].cap_b), pb = match_parts(walk, pairs[i].cap_a);
+    const int pa = match_parts(walk, pairs[i].cap_b, most);
+    const int pb = match_parts(walk, pairs[i].cap_a, most);
     L.parts_a.push_back(pa);
     L.parts_b.push_back(pb);
     L.merge = L.merge || ((pa > 1 || pb > 1) && most_rows > kMatchEmitMergeRows);
@@ -131,12 +130,11 @@ MatchLayout layout_of(int32_t n, const sift_match_pair* pairs, bool half, int st
 }
 
 // The best plan that fits: the one sift_match_workspace_size reports, then without
-// copies, then with longer parts, then without parts.
+// copies, then in fewer parts.
 MatchLayout layout_within(int32_t n, const sift_match_pair* pairs, int64_t bytes) {
-  MatchLayout L = layout_of(n, pairs, true, 1);
-  for (int stretch = 1; L.bytes > bytes && stretch <= kMatchMaxParts; stretch *= 2)
-    L = layout_of(n, pairs, false, stretch);
-  if (L.bytes > bytes) L = layout_of(n, pairs, false, 0);
+  MatchLayout L = layout_of(n, pairs, true, kMatchMaxParts);
+  for (int most = kMatchMaxParts; L.bytes > bytes && most >= 1; most /= 2)
+    L = layout_of(n, pairs, false, most);
   return L;
 }
 
@@ -148,7 +146,7 @@ sift_status sift_match_workspace_size(int32_t n, const sift_match_pair* pairs, s
   if (!bytes) return fail(SIFT_ERR_INVALID_ARG, "null bytes");
   sift_status st = check_pairs(n, pairs);
   if (st != SIFT_OK) return st;
-  *bytes = (size_t)layout_of(n, pairs, true, 1).bytes;
+  *bytes = (size_t)layout_of(n, pairs, true, kMatchMaxParts).bytes;
   return SIFT_OK;
 }
 

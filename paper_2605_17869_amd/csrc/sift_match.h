@@ -22,11 +22,12 @@ constexpr int kMatchSetupChunk = 24; // pair-table entries per setup launch
 constexpr int kMatchOwnPairs = 32;
 constexpr int kMatchMaxParts = 8;    // most parts of a walk over the other set
 
-// Parts that a walk over a set of `cap` rows is cut into, of about `walk` tiles each.
-inline int match_parts(int walk, int cap) {
+// Parts that a walk over a set of `cap` rows is cut into, of about `walk` tiles each, at
+// most `most`.
+inline int match_parts(int walk, int cap, int most) {
   const int tiles = (cap + kMatchTile - 1) / kMatchTile;
   const int parts = (tiles + walk - 1) / walk;
-  return parts < 1 ? 1 : (parts < kMatchMaxParts ? parts : kMatchMaxParts);
+  return parts < 1 ? 1 : (parts < most ? parts : most);
 }
 
 // Running nearest / second-nearest of one row or column: the best candidate

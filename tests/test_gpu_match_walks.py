@@ -43,9 +43,9 @@ def test_every_plan(sizes, counts):
             arr[k] = sm.SiftMatchPair(dev[k][0].data_ptr(), pa, na, dev[k][1].data_ptr(), pb, nb,
                                       rec.data_ptr(), cnt.data_ptr(), cnt.data_ptr() + 4, cap)
         assert lib.sift_match_workspace_size(n, arr, ctypes.byref(need)) == 0
-        least = up(96 * n) + 2 * up(4 * n + 4) + sum(
-            up(16 * na) + up(16 * nb) + up(16 * nb * ((na + 127) // 128)) for na, nb in sizes)
-        size = int(need.value - frac * max(need.value - least, 0)) // 256 * 256
+        least = up(96 * n) + 2 * up(4 * n + 4) + sum(up(16 * (na + nb)) for na, nb in sizes)
+        assert least <= need.value
+        size = int(need.value - frac * (need.value - least)) // 256 * 256
         ws = torch.empty(size + 256, dtype=torch.uint8, device="cuda").fill_(0xff)   # NaN, -1
         st = lib.sift_match_batch(n, arr, ctypes.c_float(0.8), ctypes.c_void_p(ws.data_ptr()), size,
                                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
